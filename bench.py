@@ -26,7 +26,7 @@ PEAK_VALU_OPS = 256 * 64 * 2.4e9
 # Sources of the plain-encryption kernel; the HBM traffic measured with hardware counters
 # (profiles/c2_step_hbm_counters.md) is reported only while they are unchanged.
 ENC_SOURCES = ["paper_2409_03568_amd/csrc/" + f for f in
-               ("k_ntt_impl.hpp", "k_ntt_13_enc.hip", "ntt.hpp", "modarith.hpp", "philox.hpp", "internal.hpp")]
+               ("k_ntt_impl.hpp", "k_ntt_13_enc.hip", "fft.hpp", "ntt.hpp", "modarith.hpp", "philox.hpp", "internal.hpp")]
 COUNTERS_MD = os.path.join(ROOT, "profiles", "c2_step_hbm_counters.md")
 
 
@@ -40,30 +40,29 @@ def sources_sha256():
     return h.hexdigest()
 
 
-def measured_traffic(width):
+def measured_traffic():
     """(bytes read + written per plain-encryption launch at this workload, source) from the
-    rocprofv3 FETCH_SIZE / WRITE_SIZE runs recorded in profiles/, or (None, why) when they
-    were taken at another NTT width or the kernel's sources changed since (the counters
-    cannot be read from inside this process)."""
+    rocprofv3 FETCH_SIZE / WRITE_SIZE runs recorded in profiles/, or (None, why) when the
+    kernel's sources changed since they were taken (the counters cannot be read from inside
+    this process)."""
     try:
         text = open(COUNTERS_MD).read()
     except OSError:
         return None, "no counter record"
-    m = re.search(r"traffic k_encrypt_plain_c2 width=(\d+) read_bytes=(\d+) write_bytes=(\d+) .* "
+    m = re.search(r"traffic k_encrypt_plain_c2 .*?read_bytes=(\d+) write_bytes=(\d+) .* "
                   r"sources_sha256=([0-9a-f]+)", text)
     if not m:
         return None, "no counter record"
-    if int(m.group(1)) != width:
-        return None, "counters recorded at width %s, this run uses %d" % (m.group(1), width)
-    if sources_sha256() != m.group(4):
+    if sources_sha256() != m.group(3):
         return None, "kernel sources changed since the counters were recorded"
-    return int(m.group(2)) + int(m.group(3)), ("rocprofv3 FETCH_SIZE x2.0 + WRITE_SIZE x1.0 (copy-calibrated) "
-                                               "from profiles/c2_step_hbm_counters.md, sources sha256 %s" % m.group(4)[:16])
+    return int(m.group(1)) + int(m.group(2)), ("rocprofv3 FETCH_SIZE x2.0 + WRITE_SIZE x1.0 (copy-calibrated) "
+                                               "from profiles/c2_step_hbm_counters.md, sources sha256 %s" % m.group(3)[:16])
 
 
 CONVENTION = ("FP64 VALU issue: 256 CU x 4 SIMD x 16 lanes x 2.4 GHz = 39.3 T lane-ops/s, i.e. 78.6 TFLOP/s / 2 "
-              "with an FMA counted as one op; algorithmic ops = 8 per butterfly (6-op exact modular product + sum "
-              "+ difference) and 6 per pointwise modular product")
+              "with an FMA counted as one op; algorithmic ops of an encryption = 6 per complex butterfly, 4 per complex "
+              "product and 8 per coefficient recombined modulo the prime; of a product 8 per modular butterfly (6-op "
+              "exact modular product + sum + difference) and 6 per pointwise modular product")
 
 
 def host_info():
@@ -168,14 +167,13 @@ def parse():
     return ap.parse_args()
 
 
-def ntt_ops_per_ct(log_n, L):
-    """Algorithmic FP64 VALU operations of one plain encryption: 3 transforms per limb of
-    N/2 log N butterflies (8 ops: a 6-op modular product and the sum and difference) and
-    2N pointwise modular products (6 ops) per limb."""
-    N = 1 << log_n
-    butterflies = L * 3 * (N // 2) * log_n
-    pointwise = 2 * L * N
-    return 8 * butterflies + 6 * pointwise
+def encrypt_ops_per_ct(log_n, L):
+    """Algorithmic FP64 VALU operations of one plain encryption: one complex transform of v and two
+    per polynomial and limb, on M = N/2 points (M/2 log M butterflies of 6 ops), per row two
+    products by the key and two twists (4 ops per point each), and 8 ops per coefficient to
+    recombine the pieces modulo the prime."""
+    N, M = 1 << log_n, 1 << (log_n - 1)
+    return 6 * (1 + 4 * L) * (M // 2) * (log_n - 1) + 2 * L * (4 * 4 * M + 8 * N)
 
 
 def mul_ops_per_pair(log_n, level):
@@ -622,17 +620,15 @@ def main():
         box = sum(pad[dy:dy + H, dx:dx + Wd] for dy in range(e["k"]) for dx in range(e["k"])) / (e["k"] ** 2)
         ok = float(np.max(np.abs(dec.cpu().numpy().reshape(H, Wd) - box)))
 
-    ops = ntt_ops_per_ct(c.log_n, c.num_primes) * n
+    ops = encrypt_ops_per_ct(c.log_n, c.num_primes) * n
     t_plain = phase_ms["plain"] / 1e3
     roofline = None
     if t_plain > 0:
         achieved = ops / t_plain / 1e12
         peak = PEAK_VALU_OPS / 1e12
-        width = ctx.ntt_width()
-        traffic, traffic_src = measured_traffic(width)
+        traffic, traffic_src = measured_traffic()
         roofline = {"bound": "alu",
-                    "kernel": "k_encrypt<13, %d, 1, 0, false> (fused plain encryption, %d values per thread)"
-                              % (width.bit_length() - 1, width),
+                    "kernel": "k_encrypt<13, 1, 0, false> (fused plain encryption, complex transforms)",
                     "achieved": round(achieved, 3), "peak": round(peak, 3), "unit": "TVALUop/s (FP64)",
                     "frac": round(achieved / peak, 4),
                     "traffic": traffic, "traffic_source": traffic_src, "convention": CONVENTION}
@@ -653,7 +649,7 @@ def main():
         "plain": {"ms": round(phase_ms["plain"], 3), "ct_per_s": round(n / (phase_ms["plain"] / 1e3)) if phase_ms["plain"] else None},
         "radix": {"ms": round(phase_ms["radix"], 3), "ct_per_s": round(n / (phase_ms["radix"] / 1e3)) if phase_ms["radix"] else None,
                   "GBps_write": gbs(n * S, phase_ms["radix"])},
-        "value": value_phase(phase_ms["value"], n, hits, S, ntt_ops_per_ct(c.log_n, c.num_primes)),
+        "value": value_phase(phase_ms["value"], n, hits, S, encrypt_ops_per_ct(c.log_n, c.num_primes)),
         "filter": {"ms": round(phase_ms["filter"], 3), "GBps_alg": gbs(n * S * (1 + (c.num_primes - 1) / c.num_primes),
                                                                         phase_ms["filter"])},
         "decrypt": {"ms": round(phase_ms["decrypt"], 3), "ct_per_s": round(n / (phase_ms["decrypt"] / 1e3)) if phase_ms["decrypt"] else None},

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "internal.hpp"
+#include "fft.hpp"
 #include "modarith.hpp"
 #include "philox.hpp"
 
@@ -75,7 +76,8 @@ int resolve_params(const ckks_params *p, host::Resolved *r) {
 
 void free_tables(ckks_ctx *c) {
   DevTables &d = c->dev;
-  void *ptrs[] = {d.tw_fwd, d.tw_inv, d.enc_T, d.cosj, d.cdt, d.s, d.pk, d.pk_hat, d.s_hat, d.evk, d.evk_hat, c->d_lc};
+  void *ptrs[] = {d.tw_fwd, d.tw_inv, d.cosj, d.cdt, d.s, d.pk, d.fft_fwd, d.fft_inv,
+                  d.pk_fft, d.s_fft, d.pk_hat, d.s_hat, d.evk, d.evk_hat, c->d_lc};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   d = DevTables{};
@@ -218,18 +220,21 @@ hipError_t encrypt_cached_ws(const ckks_ctx *ctx, const ckks_cache *cache, const
     return e == hipSuccess ? launch_encrypt(ctx, job, std::min<uint64_t>(n, kListGrid), st) : e;
   }
   // The misses (compute-bound full encryptions) run on the auxiliary stream beside the hit
-  // gather (bound by HBM writes); both grids are bounded so that every CU holds one
-  // encryption workgroup and one gather workgroup at once (of 1/2, 3/4, 1, 2 or 3 gather
-  // workgroups per CU, one balanced the two streams best).
+  // gather (bound by HBM writes).  The gather's grid is bounded so that it leaves the CUs room for
+  // encryptions (65,536 pixels at N = 8192, 1 or 2 workgroups per CU: 7.12 and 7.44 ms; at
+  // N = 16384, whose CUs hold one encryption, 10,000 pixels with 1 or 4: 5.3 and 4.6 ms).  The
+  // encryption's is that of a list: with one workgroup per CU the same pixels take 6.86 ms at
+  // N = 8192 when one in twelve misses, but 19.5 instead of 14.0 when three in four do.
   hipEvent_t fork = nullptr, join = nullptr;
   e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&join, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventRecord(fork, st);
   if (e == hipSuccess) e = hipStreamWaitEvent(ctx->aux, fork, 0);
-  if (e == hipSuccess) e = launch_encrypt(ctx, job, std::min<uint64_t>(n, (uint64_t)ctx->num_cus), ctx->aux);
+  if (e == hipSuccess) e = launch_encrypt(ctx, job, std::min<uint64_t>(n, kListGrid), ctx->aux);
   if (e == hipSuccess) e = hipEventRecord(join, ctx->aux);
   if (e == hipSuccess)
-    e = launch_value_gather(ctx, cache, meta, counters, hits, n, out, nullptr, st, (uint64_t)ctx->num_cus);
+    e = launch_value_gather(ctx, cache, meta, counters, hits, n, out, nullptr, st,
+                            (uint64_t)ctx->num_cus * (ctx->prm.log_n == 14 ? 4 : 1));
   if (e == hipSuccess) e = hipStreamWaitEvent(st, join, 0);
   // events may be destroyed while their work is pending; the runtime releases them after
   if (fork) (void)hipEventDestroy(fork);
@@ -384,6 +389,7 @@ int ckks_context_create(const ckks_params *params, int device, ckks_ctx **out) {
   memset(&lc, 0, sizeof(lc));
   lc.L = L;
   lc.B = r.B;
+  lc.enc_scale = ldexp(1.0, r.log_scale + 1 - r.log_n);
   double qmax = 0;
   // rows 0..L-1: the ciphertext primes; row L: the special prime of key switching (if any)
   const int rows = L + (r.qP ? 1 : 0);
@@ -419,13 +425,16 @@ int ckks_context_create(const ckks_params *params, int device, ckks_ctx **out) {
   DevTables &d = c->dev;
   if (e == hipSuccess) e = dev_alloc(&d.tw_fwd, (size_t)rows * N);
   if (e == hipSuccess) e = dev_alloc(&d.tw_inv, (size_t)rows * N);
-  if (e == hipSuccess) e = dev_alloc(&d.enc_T, (size_t)N);
   if (e == hipSuccess) e = dev_alloc(&d.cosj, (size_t)N);
-  if (e == hipSuccess) e = dev_alloc(&d.cdt, (size_t)kCdtSlots);
+  if (e == hipSuccess) e = dev_alloc(&d.cdt, (size_t)kCdtSlots + (1u << kGuideBits) / sizeof(uint64_t));
   if (e == hipSuccess) e = dev_alloc(&d.s, (size_t)N);
   if (e == hipSuccess) e = dev_alloc(&d.pk, (size_t)2 * L * N);
-  if (e == hipSuccess) e = dev_alloc(&d.pk_hat, (size_t)2 * L * N);
+  const size_t M = (size_t)N / 2;
+  for (Cplx **t : {&d.fft_fwd, &d.fft_inv, &d.s_fft})
+    if (e == hipSuccess) e = dev_alloc(t, M);
+  if (e == hipSuccess) e = dev_alloc(&d.pk_fft, (size_t)2 * L * 2 * M);
   if (e == hipSuccess) e = dev_alloc(&d.s_hat, (size_t)L * N);
+  if (e == hipSuccess && r.log_n <= 12) e = dev_alloc(&d.pk_hat, (size_t)2 * L * N);
   if (e != hipSuccess) {
     free_tables(c);
     delete c;
@@ -433,9 +442,16 @@ int ckks_context_create(const ckks_params *params, int device, ckks_ctx **out) {
   }
   if (e == hipSuccess) e = upload(d.tw_fwd, twf);
   if (e == hipSuccess) e = upload(d.tw_inv, twi);
-  if (e == hipSuccess) e = upload(d.enc_T, host::encode_table(r.log_n, r.log_scale));
   if (e == hipSuccess) e = upload(d.cosj, host::cos_table(r.log_n));
-  if (e == hipSuccess) e = upload(d.cdt, host::cdt_table(r.sigma, r.B, kCdtSlots));
+  std::vector<uint64_t> cdt = host::cdt_table(r.sigma, r.B, kCdtSlots);
+  const std::vector<uint8_t> guide = host::cdt_guide(cdt, r.B, kGuideBits, kGuideMore);
+  cdt.resize(kCdtSlots + guide.size() / sizeof(uint64_t));
+  memcpy(cdt.data() + kCdtSlots, guide.data(), guide.size());
+  if (e == hipSuccess) e = upload(d.cdt, cdt);
+  std::vector<double> ff, fi;
+  host::fft_tables(r.log_n, ff, fi);
+  if (e == hipSuccess) e = upload(reinterpret_cast<double *>(d.fft_fwd), ff);
+  if (e == hipSuccess) e = upload(reinterpret_cast<double *>(d.fft_inv), fi);
   if (e == hipSuccess) e = dev_alloc(&c->d_lc, 1);
   if (e == hipSuccess) e = hipMemcpy(c->d_lc, &c->lc, sizeof(LimbConsts), hipMemcpyHostToDevice);
   if (e == hipSuccess) {

@@ -92,57 +92,84 @@ void free_plan(ckks_batch_plan *p) {
 
 // Enqueues one run on stream st (which may be capturing).
 //
-// When limb 0 decodes exactly (the usual case), the whole batch is one pass: with a cache,
-// the metadata of every pixel is computed first, so that the hit list is ordered by pool
-// member and cache slot over the whole batch and each (entry, pool member) pair is read
-// from L2 for all its pixels at once; then one persistent launch assembles every
-// ciphertext -- cache hit, or full encryption of a miss or of every pixel without a cache
-// -- with the brightness fused in, writes it in full to a slot of the ring (of chunk_cts
-// ciphertexts, or of cts_out) and decrypts it from the registers holding its limb-0 rows.
-// With a cache that holds every value the launch has no encryption path: its workgroups
-// need only the decryption's LDS and registers, so several share a CU and one streams
-// while another transforms.  Otherwise the batch goes chunk by chunk through the ring,
-// each chunk decrypted from it with the two-limb lift.
+// Ciphertexts are written in full to the ring (of chunk_cts ciphertexts) or to cts_out, with the
+// brightness fused in, and decrypted from there.
+//
+// When limb 0 decodes exactly (the usual case), the metadata of every pixel is computed first, so
+// that the hit list is ordered by pool member and cache slot over the whole batch and each (entry,
+// pool member) pair is read from L2 for all its pixels at once; one persistent launch then
+// assembles all hits and decrypts them from the registers holding their limb-0 rows.  The misses
+// (every pixel without a cache) are encrypted and decrypted chunk by chunk through the ring; how
+// many chunks of the miss list there are is known only on the device, so the launches cover the
+// case that all pixels miss and those past the count end at once.  Otherwise the batch goes chunk by
+// chunk through the ring, each chunk decrypted from it with the two-limb lift.
 hipError_t enqueue_run(ckks_batch_plan *p, const RunKey &k, uint32_t n_seg, hipStream_t st) {
   const ckks_ctx *c = p->ctx;
   const uint64_t S = 2 * (uint64_t)c->prm.L * (uint64_t)c->N;
   const bool misses = !p->cache || p->cache->kind != CKKS_CACHE_VALUE_FULL;
   const bool whole = k.dec_limbs == 1;
-  const uint64_t chunk = whole ? k.n : p->cfg.chunk_cts;
+  const uint64_t ring = whole && k.cts ? k.n : p->cfg.chunk_cts;  // ciphertexts held at a time
+  const uint64_t chunk = whole && p->cache ? k.n : ring;
   for (uint64_t first = 0; first < k.n; first += chunk) {
     const uint64_t cnt = k.n - first < chunk ? k.n - first : chunk;
-    FusedJob job;
-    job.px = k.px + first;
-    job.n = cnt;
-    job.first_index = k.first_index + first;
-    job.seed0 = k.seed[0];
-    job.seed1 = k.seed[1];
-    job.out = k.cts ? k.cts + first * S : p->ring;
-    job.seg_end = p->seg_end;
-    job.seg_b = p->seg_b;
-    job.n_seg = n_seg;
-    job.seg_base = first;
-    job.bright_scale = ldexp(c->scale, 1 - c->prm.log_n);
-    job.cursor = p->counters + 2;
-    if (whole) {
-      job.dec_out = k.out;
-      job.inv_scale = 1.0 / c->scale;
-      job.ring = k.cts ? 0 : p->cfg.chunk_cts;
-    }
+    uint64_t *out = k.cts ? k.cts + first * S : p->ring;
     hipError_t e = hipSuccess;
     if (p->cache) {
-      e = launch_value_meta(c, p->cache, job.px, cnt, job.first_index, job.seed0, job.seed1, p->meta, p->miss,
-                            p->counters, p->hits, st);
+      e = launch_value_meta(c, p->cache, k.px + first, cnt, k.first_index + first, k.seed[0], k.seed[1], p->meta,
+                            p->miss, p->counters, p->hits, st);
+      FusedJob job;
+      job.n = cnt;
+      job.out = out;
+      job.seg_end = p->seg_end;
+      job.seg_b = p->seg_b;
+      job.n_seg = n_seg;
+      job.seg_base = first;
+      job.bright_scale = ldexp(c->scale, 1 - c->prm.log_n);
+      job.cursor = p->counters + 2;
       job.counters = p->counters;
-      job.miss_list = p->miss;
       job.hits = p->hits;
       job.meta = p->meta;
       job.entries = p->cache->entries;
       job.pool = p->cache->pool_cts;
+      if (whole) {
+        job.dec_out = k.out;
+        job.inv_scale = 1.0 / c->scale;
+        job.ring = k.cts ? 0 : ring;
+      }
+      if (e == hipSuccess) e = launch_hits_fused(c, job, st);
     }
-    if (e == hipSuccess) e = launch_cached_fused(c, job, misses, st);
+    for (uint64_t at = 0; misses && at < cnt && e == hipSuccess; at += ring) {
+      const uint64_t m = cnt - at < ring ? cnt - at : ring;
+      EncJob job;
+      job.px = k.px + first;
+      job.n = m;
+      job.first_index = k.first_index + first;
+      job.seed0 = k.seed[0];
+      job.seed1 = k.seed[1];
+      job.out = out;
+      job.seg_end = p->seg_end;
+      job.seg_b = p->seg_b;
+      job.n_seg = n_seg;
+      job.seg_base = first;
+      job.bright_scale = ldexp(c->scale, 1 - c->prm.log_n);
+      DecJob dec;
+      if (p->cache) {
+        job.list = dec.list = p->miss;
+        job.list_count = dec.list_count = p->counters;
+        job.list_first = dec.list_first = at;
+        job.compact = dec.compact = whole && !k.cts;
+      }
+      e = launch_encrypt(c, job, p->cache ? std::min(m, kListGrid) : m, st);
+      if (e != hipSuccess || !whole) continue;
+      dec.cts = out;
+      dec.n = m;
+      dec.level = c->prm.L;
+      dec.inv_scale = 1.0 / c->scale;
+      dec.out = k.out + first;
+      e = launch_decrypt(c, dec, 1, st, p->cache ? kListGrid : 0);
+    }
     if (e == hipSuccess && !whole)
-      e = launch_decrypt(c, job.out, cnt, c->prm.L, c->scale, k.out + first, k.dec_limbs, st);
+      e = launch_decrypt(c, out, cnt, c->prm.L, c->scale, k.out + first, k.dec_limbs, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -162,6 +162,19 @@ std::vector<uint64_t> cdt_table(double sigma, int B, int slots) {
   return T;
 }
 
+std::vector<uint8_t> cdt_guide(const std::vector<uint64_t> &cdt, int B, int bits, uint8_t more) {
+  std::vector<uint8_t> g((size_t)1 << bits);
+  for (size_t i = 0; i < g.size(); i++) {
+    const uint64_t first = (uint64_t)i << (64 - bits), last = first + ((1ULL << (64 - bits)) - 1);
+    int at = 0, upto = 0;
+    while (at < 2 * B && cdt[(size_t)at] <= first) at++;
+    upto = at;
+    while (upto < 2 * B && cdt[(size_t)upto] <= last) upto++;
+    g[i] = (uint8_t)(at | (upto - at > 1 || last == ~0ULL ? more : 0));
+  }
+  return g;
+}
+
 std::vector<double> encode_table(int log_n, int log_scale) {
   const int N = 1 << log_n;
   std::vector<double> T((size_t)N);
@@ -200,6 +213,58 @@ void twiddles(uint64_t q, uint64_t psi, int log_n, std::vector<double> &fwd, std
     fwd[(size_t)k] = centered(pw[b], q);
     inv[(size_t)k] = centered(ipw[b], q);
   }
+}
+
+void fft_tables(int log_n, std::vector<double> &fwd, std::vector<double> &inv) {
+  const int lm = log_n - 1;
+  const int64_t M = (int64_t)1 << lm, T = M / 16;
+  // every factor is a power of exp(i pi / 2M): its first octant from extended precision, the
+  // others by symmetry
+  std::vector<double> c((size_t)(M / 2 + 1)), s((size_t)(M / 2 + 1));
+  const long double step = acosl(-1.0L) / (long double)(2 * M);
+  for (int64_t n = 0; n <= M / 2; n++) {
+    c[(size_t)n] = (double)cosl(step * (long double)n);
+    s[(size_t)n] = (double)sinl(step * (long double)n);
+  }
+  auto put = [&](std::vector<double> &t, int64_t at, int64_t n) {  // exp(i pi n / 2M)
+    n &= 4 * M - 1;
+    const int64_t quarter = n / M, r = n % M;
+    const bool mirror = r > M / 2;
+    const size_t k = (size_t)(mirror ? M - r : r);
+    double re = mirror ? s[k] : c[k], im = mirror ? c[k] : s[k];
+    for (int64_t i = 0; i < quarter; i++) {  // times i
+      const double x = re;
+      re = -im;
+      im = x;
+    }
+    t[(size_t)(2 * at)] = re;
+    t[(size_t)(2 * at + 1)] = im;
+  };
+  fwd.assign((size_t)(2 * M), 0.0);
+  inv.assign((size_t)(2 * M), 0.0);
+  // Forward: the level at element bit `bit` has the factor exp(i pi (1/4 + brv(node)) / 2^stage),
+  // stage = lm - 1 - bit and node the element bits above: 2^bit, plus 2^(lm - i) for each set
+  // node bit i, in units of pi / 2M.
+  auto node = [&](int bit, int64_t e) {
+    int64_t n = (int64_t)1 << bit;
+    for (int i = 0; bit + 1 + i < lm; i++)
+      if ((e >> (bit + 1 + i)) & 1) n += (int64_t)1 << (lm - i);
+    return n;
+  };
+  const bool trade = lm - 8 > 4;  // the top pass has five levels (N = 2^14)
+  put(fwd, 0, node(trade ? 9 : 8, 0));
+  for (int64_t l = 0; l < 2 && trade; l++) put(fwd, 2 + l, node(8, l << 12));
+  int64_t at = 4;
+  for (int base : {4, 0}) {
+    const int64_t H = (int64_t)1 << (lm - base - 4);
+    for (int64_t h = 0; h < H; h++) put(fwd, at + h, node(base, h << (base + 4)));
+    at += H;
+  }
+  // Inverse: distance 2^bit, offset p: exp(-i pi p / 2^bit).
+  auto offset = [&](int bit, int64_t p) { return -(p << (lm + 1 - bit)); };
+  for (int64_t p = 0; p < T; p++) put(inv, p, offset(lm - 1, p));
+  for (int64_t p = 0; p < 256 && trade; p++) put(inv, T + p, offset(8, p));
+  for (int64_t p = 0; p < 16; p++) put(inv, T + 256 + p, offset(7, p));
 }
 
 }  // namespace host

@@ -38,6 +38,10 @@ uint64_t shoup_companion(uint64_t w, uint64_t q);  // floor(w * 2^64 / q)
 
 // Gaussian cumulative table (2B entries) padded with all-ones to `slots` entries.
 std::vector<uint64_t> cdt_table(double sigma, int B, int slots);
+// Guide into it on the top `bits` bits of a word (gauss_guided in philox.hpp): the count of
+// thresholds at most the range's first word, plus `more` when the range holds a threshold after
+// the next one, or the all-ones word (which the padding would count).
+std::vector<uint8_t> cdt_guide(const std::vector<uint64_t> &cdt, int B, int bits, uint8_t more);
 // T_j = 2^(log_scale + 1 - log_n) cos(pi j / N) and cos(pi j / N).
 std::vector<double> encode_table(int log_n, int log_scale);
 std::vector<double> cos_table(int log_n);
@@ -45,6 +49,10 @@ std::vector<double> cos_table(int log_n);
 // Twiddles for the merged-psi transforms, stored as centered doubles:
 // fwd[k] = psi^brv(k), inv[k] = psi^-brv(k), k < N.
 void twiddles(uint64_t q, uint64_t psi, int log_n, std::vector<double> &fwd, std::vector<double> &inv);
+
+// Factors of the complex transforms (fft.hpp) of N = 2^log_n coefficients, M = N/2 complex
+// values per direction as interleaved real and imaginary parts.
+void fft_tables(int log_n, std::vector<double> &fwd, std::vector<double> &inv);
 
 // Centered double representative of a residue.
 double centered(uint64_t r, uint64_t q);

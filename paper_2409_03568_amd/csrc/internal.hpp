@@ -33,18 +33,24 @@ struct LimbConsts {
   double pinv[kMaxL];        // qP^-1 mod q_i, centered (ModDown)
   double pmod[kMaxL];        // qP mod q_i, centered (the s^2 term of key-switching key i)
   double q0inv_q1;           // q_0^-1 mod q_1, centered (two-limb CRT of decryption)
+  double enc_scale;          // scale * 2^(1 - log N): value v encodes as rint(v enc_scale cos(pi j / N))
 };
+
+struct Cplx;  // complex double (fft.hpp)
 
 // Device tables owned by a context.
 struct DevTables {
   double *tw_fwd = nullptr;  // [L+1][N] (row L: the special prime)
   double *tw_inv = nullptr;  // [L+1][N]
-  double *enc_T = nullptr;   // [N] encoding table at scale Delta
   double *cosj = nullptr;    // [N] cos(pi j / N)
-  uint64_t *cdt = nullptr;   // [kCdtSlots]
+  uint64_t *cdt = nullptr;   // [kCdtSlots], then the guide of 2^kGuideBits bytes
   int64_t *s = nullptr;      // [N] secret key
   uint64_t *pk = nullptr;    // [2][L][N] public key, coefficient domain
-  double *pk_hat = nullptr;  // [2][L][N] NTT domain times N^-1, centered
+  // Complex transforms (fft.hpp), M = N/2 points each
+  Cplx *fft_fwd = nullptr, *fft_inv = nullptr;  // [M] factors
+  Cplx *pk_fft = nullptr;    // [2][L][2][M] transforms of the low and high pieces of pk, times 1/M
+  Cplx *s_fft = nullptr;     // [M] transform of s, times 1/M
+  double *pk_hat = nullptr;  // [2][L][N] NTT domain times N^-1, centered (N <= 4096)
   double *s_hat = nullptr;   // [L][N] NTT domain times N^-1, centered
   uint64_t *evk = nullptr;   // [L][L+1][2][N] key-switching keys of s^2, coefficient domain
   double *evk_hat = nullptr; // [L][L+1][2][N] the same in the NTT domain times N^-1, centered
@@ -61,6 +67,8 @@ struct EncJob {
   const uint64_t *ts = nullptr;
   const uint32_t *list = nullptr;
   const uint32_t *list_count = nullptr;
+  uint64_t list_first = 0;      // list: from this position of the list, at most n items
+  bool compact = false;         // list: the i-th of them goes to out[i], not to out[item]
   uint64_t n = 0;
   uint64_t first_index = 0;
   uint64_t seed0 = 0, seed1 = 0;
@@ -75,18 +83,28 @@ struct EncJob {
   double bright_scale = 0.0;
 };
 
-// Cached encryption in one persistent launch (k_cached_fused): misses miss_list[0..counters[0])
-// are encrypted in full, hits hits[0..counters[1]) are entry + pool member as meta[pixel]
-// says; without a cache (counters == NULL) every pixel 0..n-1 is encrypted in full.
-// Optional fused brightness (seg_* as in EncJob) and decryption of limb 0 into dec_out.
-struct FusedJob {
-  const uint8_t *px = nullptr;
+// What to decrypt: ciphertexts cts[0..n), or those of items list[list_first..), at most n of them
+// and up to *list_count, found at cts[item], or with `compact` at cts[0..).  The value of an item
+// goes to out[item].
+struct DecJob {
+  const uint64_t *cts = nullptr;
   uint64_t n = 0;
-  uint64_t first_index = 0;
-  uint64_t seed0 = 0, seed1 = 0;
+  int level = 0;
+  double inv_scale = 0.0;
+  double *out = nullptr;
+  const uint32_t *list = nullptr;
+  const uint32_t *list_count = nullptr;
+  uint64_t list_first = 0;
+  bool compact = false;
+};
+
+// Cache hits in one persistent launch (k_hits_fused): pixels hits[0..counters[1]) (at most n) are
+// entry + pool member as meta[pixel] says, plus the brightness of their image (seg_* as in
+// EncJob), optionally with the decryption of limb 0 into dec_out.
+struct FusedJob {
+  uint64_t n = 0;
   uint64_t *out = nullptr;               // [n][2][L][N]
-  const uint32_t *counters = nullptr;    // [miss count, hit count], or NULL: every pixel a miss
-  const uint32_t *miss_list = nullptr;
+  const uint32_t *counters = nullptr;    // [miss count, hit count]
   const uint32_t *hits = nullptr;
   const uint32_t *meta = nullptr;
   const uint64_t *entries = nullptr;
@@ -281,16 +299,14 @@ hipError_t run_tiles(const ckks_ctx *ctx, const ckks_cache *cache, const uint8_t
                      const uint64_t *K, double out_scale, int dec_limbs, double *d_out, void *mem, hipStream_t st);
 
 // Launchers (return a hipError_t; enqueue on `stream`).
-// misses = false: the cache holds every value (VALUE_FULL), so only hits occur; the kernel
-// is then compiled without the encryption path (decryption-sized LDS and registers) and
-// uses the decryption's NTT width.
-hipError_t launch_cached_fused(const ckks_ctx *c, const FusedJob &job, bool misses, hipStream_t stream);
+hipError_t launch_hits_fused(const ckks_ctx *c, const FusedJob &job, hipStream_t stream);
 hipError_t launch_keygen(const ckks_ctx *c, uint64_t seed0, uint64_t seed1, hipStream_t stream);
 hipError_t launch_keys_prepare(const ckks_ctx *c, hipStream_t stream);
 hipError_t launch_encrypt(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t stream);
 // limbs = 1: decode the centered residue of limb 0; limbs = 2 (level >= 2): decode the
 // centered CRT lift of limbs 0 and 1.  max_grid (0 = no bound): at most this many
 // workgroups, each taking every max_grid-th ciphertext.
+hipError_t launch_decrypt(const ckks_ctx *c, const DecJob &job, int limbs, hipStream_t stream, uint64_t max_grid = 0);
 hipError_t launch_decrypt(const ckks_ctx *c, const uint64_t *cts, uint64_t n, int level, double scale, double *out,
                           int limbs, hipStream_t stream, uint64_t max_grid = 0);
 // Key-switching keys of s^2 (grid: digits x primes), then their NTT-domain copies.

@@ -21,7 +21,7 @@ __global__ void __launch_bounds__(1 << (LOGN - LOGR))
   using Red = Schedule<LOGN, RC>;
   constexpr int N = S::N, R = S::R, T = S::T;
   const LimbConsts &lc = *lcp;
-  extern __shared__ double lds[];
+  extern __shared__ __attribute__((aligned(128))) double lds[];
   uint64_t *cdt = reinterpret_cast<uint64_t *>(lds + S::SLOTS);
   uint16_t *lds16 = reinterpret_cast<uint16_t *>(lds);
   const int tid = threadIdx.x;
@@ -91,7 +91,7 @@ __global__ void __launch_bounds__(1 << (LOGN - LOGR))
   using Red = Schedule<LOGN, RC>;
   constexpr int N = S::N, R = S::R, T = S::T;
   const LimbConsts &lc = *lcp;
-  extern __shared__ double lds[];
+  extern __shared__ __attribute__((aligned(128))) double lds[];
   const int tid = threadIdx.x, i = blockIdx.x, j = blockIdx.y, k = blockIdx.z, L = lc.L;
   const double q = lc.q[j], qinv = lc.qinv[j];
   const size_t off = ((((size_t)i * (L + 1) + j) * 2) + k) * N;
@@ -128,7 +128,7 @@ __global__ void __launch_bounds__(1 << (LOGN - LOGR))
   using Red = Schedule<LOGN, RC>;
   constexpr int N = S::N, R = S::R, T = S::T;
   const LimbConsts &lc = *lcp;
-  extern __shared__ double lds[];
+  extern __shared__ __attribute__((aligned(128))) double lds[];
   const int L = lc.L;
   const uint64_t S_ct = (uint64_t)2 * level * N;
   // scratch of this workgroup, every element written and read by one thread:

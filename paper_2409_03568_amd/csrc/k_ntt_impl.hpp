@@ -1,13 +1,17 @@
-// NTT-based kernels: key generation, key preparation, fused per-pixel encryption and
-// decryption.  One workgroup handles one ciphertext at a time (all limbs), so the
-// random polynomials v, e0, e1 are drawn once per ciphertext and reused by every limb.
+// Transform-based kernels: key generation (prime-field NTT, ntt.hpp) and key preparation,
+// fused per-pixel encryption and decryption (complex transforms, fft.hpp).  One workgroup
+// handles one ciphertext at a time (all limbs), so the random polynomials v, e0, e1 are drawn,
+// and v transformed, once per ciphertext and reused by every limb.
 //
-// Template parameters: LOGN (ring degree), LOGR (values per thread, so N / 2^LOGR threads
-// per workgroup) and RC (reduction class of the primes, see ntt.hpp).  Each ring degree is
-// instantiated in its own translation unit (k_ntt_<LOGN>.hip).
+// Template parameters: LOGN (ring degree), RC (class of the primes' sizes, see ntt.hpp and
+// Split) and, for the kernels on prime-field transforms, LOGR (values per thread, so
+// N / 2^LOGR threads per workgroup).  Each ring degree is instantiated in its own translation
+// units (k_ntt_<LOGN>_*.hip).
 #pragma once
+#include <algorithm>
 #include <atomic>
 
+#include "fft.hpp"
 #include "internal.hpp"
 #include "ntt.hpp"
 #include "philox.hpp"
@@ -21,43 +25,41 @@ struct Shape : NttShape<LOGN, LOGR> {
   // table, and a reduction area
   static constexpr int SLOTS = LdsSlots<LOGN, LOGR>::value;
   static constexpr size_t lds_bytes = sizeof(double) * ((size_t)SLOTS + kCdtSlots + 64);
-  // Encryption also keeps the packed samples of the current ciphertext (2 bytes per
-  // coefficient) in LDS when that fits a CU's 160 KiB, instead of in registers for the
-  // whole ciphertext.
-  static constexpr size_t smp_bytes = sizeof(uint16_t) * ((size_t)1 << LOGN);
-  // When a second exchange space fits as well (N <= 8192), encryption runs the two
-  // inverse transforms of a limb as one paired transform; its second space follows the
-  // reduction area, and the packed samples follow that when they fit too.
-  static constexpr bool kDual = lds_bytes + sizeof(double) * (size_t)SLOTS <= 160 * 1024;
-  static constexpr size_t enc_base_bytes = lds_bytes + (kDual ? sizeof(double) * (size_t)SLOTS : 0);
-  static constexpr bool kSmpLds = enc_base_bytes + smp_bytes <= 160 * 1024;
-  static constexpr size_t enc_lds_bytes = enc_base_bytes + (kSmpLds ? smp_bytes : 0);
+  // encryption: then a second exchange space (the two inverse transforms of a limb run as one
+  // paired transform), the packed samples of the current ciphertext and the guide
+  static constexpr size_t enc_smp_at = lds_bytes + sizeof(double) * (size_t)SLOTS;
+  static constexpr size_t enc_guide_at = enc_smp_at + sizeof(uint16_t) * ((size_t)1 << LOGN);
+  static constexpr size_t enc_lds_bytes = enc_guide_at + (1 << kGuideBits);
 };
 
 // Draw the packed samples of one polynomial triple into LDS: word j of dst holds
 // coefficient j as (t1 + 1) | (g2 + B) << 2 | (g3 + B) << 9, where t1 is the ternary
 // value of stream tag1 and g2, g3 the Gaussian values of streams tag2, tag3 (all at
-// Philox index t; 0 <= g + B <= 2B <= 126).  Each thread draws whole Philox blocks; ends
-// with a barrier.
+// Philox index t; 0 <= g + B <= 2B <= 126; streams that are not used leave any value).  Each of
+// `threads` threads draws whole Philox blocks; ends with a barrier.  GUIDED: with the guide of gauss_guided.
 constexpr int kSmpShiftG2 = 2, kSmpShiftG3 = 9;
 
-template <int LOGN, int LOGR>
-__device__ __forceinline__ void draw_samples(uint16_t *dst, const uint64_t *cdt, int B, int tid, uint64_t k0,
-                                             uint64_t k1, uint64_t t, uint32_t tag1, uint32_t tag2, uint32_t tag3) {
-  using S = NttShape<LOGN, LOGR>;
-  static_assert(S::R >= 4, "each thread draws whole Philox blocks");
+template <int LOGN, bool GUIDED>
+__device__ __forceinline__ void draw_samples(uint16_t *dst, const uint64_t *cdt, int B, int tid, int threads,
+                                             uint64_t k0, uint64_t k1, uint64_t t, uint32_t tag1, uint32_t tag2,
+                                             uint32_t tag3, bool use2, bool use3, const uint8_t *guide) {
 #pragma unroll 1
-  for (int kk = 0; kk < S::R / 4; kk++) {
-    const uint32_t b = (uint32_t)(tid + S::T * kk);
+  for (uint32_t b = (uint32_t)tid; b < (1u << LOGN) / 4; b += (uint32_t)threads) {
     const Philox4 pv = philox4x64_10(t, tag1, b, 0, k0, k1);
-    const Philox4 pa = philox4x64_10(t, tag2, b, 0, k0, k1);
-    const Philox4 pb = philox4x64_10(t, tag3, b, 0, k0, k1);
+    const Philox4 pa = use2 ? philox4x64_10(t, tag2, b, 0, k0, k1) : Philox4{};
+    const Philox4 pb = use3 ? philox4x64_10(t, tag3, b, 0, k0, k1) : Philox4{};
     uint32_t w2[2];
 #pragma unroll
     for (int w = 0; w < 4; w++) {
       const uint32_t tv = (uint32_t)(ternary_of(pv.w[w]) + 1);
-      const uint32_t ga = (uint32_t)(gauss_of(pa.w[w], cdt, B) + B);
-      const uint32_t gb = (uint32_t)(gauss_of(pb.w[w], cdt, B) + B);
+      uint32_t ga, gb;
+      if constexpr (GUIDED) {
+        ga = gauss_guided(pa.w[w], cdt, guide, B);
+        gb = gauss_guided(pb.w[w], cdt, guide, B);
+      } else {
+        ga = (uint32_t)(gauss_of(pa.w[w], cdt, B) + B);
+        gb = (uint32_t)(gauss_of(pb.w[w], cdt, B) + B);
+      }
       const uint32_t word = tv | (ga << kSmpShiftG2) | (gb << kSmpShiftG3);
       w2[w >> 1] = (w & 1) ? (w2[w >> 1] | (word << 16)) : word;
     }
@@ -72,7 +74,7 @@ __device__ __forceinline__ void draw_samples(uint32_t (&smp)[1 << LOGR], uint16_
                                              int B, int tid, uint64_t k0, uint64_t k1, uint64_t t, uint32_t tag1,
                                              uint32_t tag2, uint32_t tag3) {
   using S = NttShape<LOGN, LOGR>;
-  draw_samples<LOGN, LOGR>(lds16, cdt, B, tid, k0, k1, t, tag1, tag2, tag3);
+  draw_samples<LOGN, false>(lds16, cdt, B, tid, S::T, k0, k1, t, tag1, tag2, tag3, true, true, nullptr);
 #pragma unroll
   for (int r = 0; r < S::R; r++) smp[r] = lds16[tid + S::T * r];
 }
@@ -81,9 +83,22 @@ __device__ __forceinline__ int smp_t(uint32_t s) { return (int)(s & 3u) - 1; }
 __device__ __forceinline__ int smp_g(uint32_t s, int shift, int B) { return (int)((s >> shift) & 0x7fu) - B; }
 
 // ---------------------------------------------------------------------------
-// fused plain encryption: per ciphertext, per limb
-//   x = NTT(v); c0 = INTT(x * pk0^) + e0 + m; c1 = INTT(x * pk1^) + e1
+// fused plain encryption: c0 = v pk0 + e0 + m, c1 = v pk1 + e1 per limb.  v is transformed
+// once; each row (one polynomial of one limb) takes the two inverse transforms of its pieces
+// (see fft.hpp).
 // ---------------------------------------------------------------------------
+// LDS of the complex-transform kernels: the exchange space of N doubles (it also holds the
+// Gaussian table while samples are drawn, and the decoding's sums); encryption adds the packed
+// samples of the current ciphertext (2 bytes per coefficient), which N = 2^14 keeps in
+// registers.  At N = 8192 that is 80 KiB: two workgroups share a CU, and one's arithmetic covers
+// the other's barriers and loads.
+template <int LOGN>
+struct FftLds {
+  static constexpr size_t exchange = sizeof(double) << LOGN;
+  static constexpr bool kSmp = LOGN <= 13;
+  static constexpr size_t encrypt = exchange + (kSmp ? sizeof(uint16_t) << LOGN : 0);
+};
+
 // Where item i's pixel value and Philox index come from (compiled separately, so each
 // variant keeps only the pointers it reads live):
 //   kEncPixels:  items 0..n-1, value px[i], index first_index + i;
@@ -93,26 +108,322 @@ __device__ __forceinline__ int smp_g(uint32_t s, int shift, int B) { return (int
 // BRIGHT adds the image's brightness encoding to c0 (EncJob::seg_b).
 enum EncMode : int { kEncPixels = 0, kEncList = 1, kEncEntries = 2 };
 
-// One limb of the encryption of the current item, by the whole workgroup (the samples
-// are drawn): x = NTT(v); c0 = INTT(x pk0^) + e0 + m (+ the brightness encoding fb);
-// c1 = INTT(x pk1^) + e1, stored to out.  With KEEP the canonical values of c0 and c1 are
-// also returned in k0 / k1 (first-pass layout: register r holds coefficient tid + T r).
-template <int LOGN, int LOGR, int RC, bool BRIGHT, bool KEEP>
-__device__ __forceinline__ void encrypt_limb(int l, double *lds, const uint16_t *smpl, const uint32_t (&smp)[1 << LOGR],
-                                             int L, int B, double value, double fb, uint64_t *out,
-                                             const LimbConsts &lc, const DevTables &dt, double (&k0)[1 << LOGR],
-                                             double (&k1)[1 << LOGR]) {
+// One encryption: its ciphertext's place, Philox index, and the factors of the encodings of its
+// value and brightness, rint(fv cos(pi j / N)) with fv = value 2^(1 - log N) scale, exact as the
+// value times a power of two.
+struct EncItem {
+  uint64_t slot, t;
+  double fv, fb;
+};
+template <int MODE>
+__device__ __forceinline__ uint64_t enc_count(const EncJob &job) {
+  if (MODE == kEncEntries && job.list_count) return *job.list_count;
+  if (MODE != kEncList) return job.n;
+  const uint64_t m = *job.list_count, left = m > job.list_first ? m - job.list_first : 0;
+  return left < job.n ? left : job.n;
+}
+template <int MODE, bool BRIGHT>
+__device__ __forceinline__ EncItem enc_item(const EncJob &job, uint64_t it, const LimbConsts &lc) {
+  const uint64_t item = MODE == kEncList ? (uint64_t)job.list[job.list_first + it] : it;
+  EncItem e;
+  e.slot = MODE == kEncList && job.compact ? it : item;
+  e.t = MODE == kEncEntries ? job.ts[item] : job.first_index + item;
+  e.fv = (MODE == kEncEntries ? (double)job.vals[item] : (double)job.px[item]) * lc.enc_scale;
+  e.fb = BRIGHT ? job.seg_b[segment_of(job.seg_end, job.n_seg, job.seg_base + item)] * job.bright_scale : 0.0;
+  return e;
+}
+
+// The samples of one encryption: packed words of coefficients p + T r (p the thread's place),
+// in LDS or in registers.
+template <int LOGN>
+struct Samples {
+  const uint16_t *lds;
+  uint32_t reg[FftLds<LOGN>::kSmp ? 1 : 32];
+  __device__ __forceinline__ uint32_t at(int r, int p) const {
+    if constexpr (FftLds<LOGN>::kSmp)
+      return (uint32_t)lds[p + Fft<LOGN>::T * r];
+    else
+      return reg[r];
+  }
+};
+
+// Draws the samples of encryption t (the Gaussian ones of e0 and e1 if asked for) with the
+// `threads` threads of the workgroup.  The Gaussian tables are staged in the exchange space, which
+// another wave may still be using for an earlier item.
+template <int LOGN>
+__device__ __forceinline__ void draw_item(Samples<LOGN> &smp, double *lds, int B, uint64_t k0, uint64_t k1, uint64_t t,
+                                          int threads, bool e0, bool e1, const DevTables &dt) {
+  using F = Fft<LOGN>;
+  const int tid = opaque(threadIdx.x);
+  constexpr int kTable = kCdtSlots + (1 << kGuideBits) / (int)sizeof(uint64_t);  // thresholds and guide
+  uint64_t *cdt = reinterpret_cast<uint64_t *>(lds);
+  uint16_t *words = FftLds<LOGN>::kSmp ? reinterpret_cast<uint16_t *>(lds + 2 * F::M)
+                                       : reinterpret_cast<uint16_t *>(cdt + kTable);
+  __syncthreads();
+  for (int i = tid; i < kTable / 2; i += threads)
+    reinterpret_cast<u64x2 *>(cdt)[i] = reinterpret_cast<const u64x2 *>(dt.cdt)[i];
+  __syncthreads();
+  draw_samples<LOGN, true>(words, cdt, B, tid, threads, k0, k1, t, kTagV, kTagE0, kTagE1, e0, e1,
+                           reinterpret_cast<const uint8_t *>(cdt + kCdtSlots));
+  smp.lds = words;
+  if constexpr (!FftLds<LOGN>::kSmp) {
+    const int p = (int)fft_place<LOGN>((unsigned)tid);
+#pragma unroll
+    for (int r = 0; r < 32; r++) smp.reg[r] = words[p + F::T * r];
+  }
+}
+
+// v_hat of the current item, in transform order.
+template <int LOGN>
+__device__ __forceinline__ void encrypt_forward(double (&v)[1][2][16], double *lds, const Samples<LOGN> &smp,
+                                                const DevTables &dt) {
+  const int tid = opaque(threadIdx.x), p = (int)fft_place<LOGN>((unsigned)tid);
+#pragma unroll
+  for (int r = 0; r < 32; r++) v[0][r >> 4][r & 15] = (double)smp_t(smp.at(r, p));
+  fft_forward<LOGN, 1>(v, lds, tid, dt.fft_fwd);
+#pragma unroll
+  for (int r = 0; r < 32; r++) computed_here(v[0][r >> 4][r & 15]);
+}
+
+// A quarter of a row's key values: both pieces of values 4 part .. 4 part + 3.
+struct KeyPart {
+  Cplx k[4][2];
+};
+template <int LOGN>
+__device__ __forceinline__ const Cplx *key_row(int poly, int l, int L, const DevTables &dt) {
+  return dt.pk_fft + ((size_t)poly * L + l) * 2 * Fft<LOGN>::M;
+}
+template <int LOGN>
+__device__ __forceinline__ KeyPart load_part(const Cplx *key, int part) {
+  using F = Fft<LOGN>;
+  const unsigned tid = (unsigned)opaque(threadIdx.x);
+  KeyPart o;
+#pragma unroll
+  for (int r = 0; r < 4; r++)
+#pragma unroll
+    for (int i = 0; i < 2; i++) o.k[r][i] = ld_row(key + i * F::M + (4 * part + r) * F::T, tid);
+  return o;
+}
+__device__ __forceinline__ void row_product(double (&x)[2][2][16], const double (&v)[1][2][16], const KeyPart &o, int part) {
+#pragma unroll
+  for (int r = 0; r < 4; r++)
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      const int at = 4 * part + r;
+      const double vr = v[0][0][at], vi = v[0][1][at];
+      x[i][0][at] = __builtin_fma(vr, o.k[r][i].re, -(vi * o.k[r][i].im));
+      x[i][1][at] = __builtin_fma(vr, o.k[r][i].im, vi * o.k[r][i].re);
+      computed_here(x[i][0][at]);
+      computed_here(x[i][1][at]);
+    }
+  stage_fence();
+}
+
+// Half of a row's results: coefficients p + T r and p + T r + M of values r = 8 h .. 8 h + 7.
+struct RowHalf {
+  uint64_t w[2][8];
+};
+template <int LOGN>
+__device__ __forceinline__ void store_half(uint64_t *row, const RowHalf &res, int h) {
+  using F = Fft<LOGN>;
+  const unsigned p = fft_place<LOGN>((unsigned)opaque(threadIdx.x));
+#pragma unroll
+  for (int im = 0; im < 2; im++)
+#pragma unroll
+    for (int r = 0; r < 8; r++)
+      __builtin_nontemporal_store(res.w[im][r], row_at(row + F::T * (8 * h + r) + F::M * im, p));
+  stage_fence();
+}
+
+// One row of the encryption of the current item, by the whole workgroup: v pk + e of polynomial
+// POLY of limb l, plus, on polynomial 0, the encodings rint(fv cos) of the value and
+// rint(fb cos) of the brightness, written to `row`.  A wave's loads and stores complete in order,
+// so a load issued after stores waits for them; therefore the first quarter of the keys comes
+// loaded by the caller, the second half of the results is left to be stored by the next row
+// (res, to `before` unless that is NULL) once its own keys are on their way, and the first half is
+// stored when no load of this row is left.
+template <int LOGN, int RC, int POLY, bool BRIGHT>
+__device__ __forceinline__ void encrypt_row(RowHalf &res, uint64_t *before, uint64_t *row, const KeyPart &first, int l,
+                                            int L, const double (&v)[1][2][16], double *lds, const Samples<LOGN> &smp,
+                                            int B, double fv, double fb, const LimbConsts &lc, const DevTables &dt) {
+  using F = Fft<LOGN>;
+  constexpr double unit = Split<RC>::unit;
+  const int tid = opaque(threadIdx.x);
+  double x[2][2][16];  // low and high piece
+  row_product(x, v, first, 0);
+  {
+    const Cplx *key = key_row<LOGN>(POLY, l, L, dt);
+    const KeyPart k1 = load_part<LOGN>(key, 1), k2 = load_part<LOGN>(key, 2);
+    stage_fence();
+    row_product(x, v, k1, 1);
+    const KeyPart k3 = load_part<LOGN>(key, 3);
+    stage_fence();
+    if (before) store_half<LOGN>(before, res, 1);
+    row_product(x, v, k2, 2);
+    row_product(x, v, k3, 3);
+  }
+  // The twist of value r is (cos, cos) of coefficients j and j + M, the factors of the encodings
+  // as well: polynomial 0 loads them all, polynomial 1 forms them from the first.
+  const int p = (int)fft_place<LOGN>((unsigned)opaque(threadIdx.x));
+  Cplx t[POLY == 0 ? 16 : 1];
+  auto load_twist = [&](int r) {
+    return Cplx{*row_at(dt.cosj + F::T * r, (unsigned)p), *row_at(dt.cosj + F::M + F::T * r, (unsigned)p)};
+  };
+  fft_inverse<LOGN, 2>(x, lds, tid, dt.fft_inv, [&] {
+    t[0] = load_twist(0);
+    if constexpr (POLY == 0) {
+#pragma unroll
+      for (int r = 1; r < 4; r++) t[r] = load_twist(r);
+    }
+  });
+  const double q = lc.q[l], qinv = lc.qinv[l], qinv_u = qinv * unit, b = (double)B;
+#pragma unroll
+  for (int r = 0; r < 16; r++) {
+    if constexpr (POLY == 0) {
+      if (r % 4 == 0 && r < 8) {  // the next four, and before the first stores all
+#pragma unroll
+        for (int i = 4; i < (r == 4 ? 12 : 8); i++) t[(r + i) % 16] = load_twist(r + i);
+        stage_fence();
+      }
+    }
+    Cplx tw;
+    if constexpr (POLY == 0)
+      tw = t[r];
+    else
+      tw = fft_twist(t[0], r);
+#pragma unroll
+    for (int im = 0; im < 2; im++) {
+      const double tr = im ? tw.im : tw.re, ti = im ? tw.re : -tw.im;
+      // the error with its offset B, and the encodings, join the low piece before it is rounded
+      double add = (double)((smp.at(r + 16 * im, p) >> (POLY == 0 ? kSmpShiftG2 : kSmpShiftG3)) & 0x7fu);
+      if constexpr (POLY == 0) {
+        add += __builtin_rint(fv * tr);
+        if (BRIGHT) add += __builtin_rint(fb * tr);
+      }
+      const double lo = __builtin_fma(tr, x[0][0][r], __builtin_fma(ti, x[0][1][r], add));
+      const double hi = __builtin_rint(__builtin_fma(tr, x[1][0][r], ti * x[1][1][r]));
+      double c;  // c0 or c1, plus B, in (-q, q)
+      if constexpr (RC == 0 && LOGN <= 12) {
+        // |v pk| <= N q/2 <= 2^51: the sum of the pieces is exact
+        const double y = __builtin_fma(hi, unit, __builtin_rint(lo));
+        c = __builtin_fma(-__builtin_rint(y * qinv), q, y);
+      } else if constexpr (RC == 1 && POLY == 1) {
+        // |low piece| <= N 2^24 + 2B < q/2 (q > 2^40): the high piece alone gives the quotient
+        c = __builtin_fma(-__builtin_rint(hi * qinv_u), q, hi * unit) + lo;
+      } else {
+        c = fft_combine(hi, lo, unit, q, qinv, qinv_u);
+      }
+      // without B, wrapped to [0, q) and rounded by the addition of 2^52: before it the low piece
+      // was off its integer by under 2^-5, and the sums of magnitudes up to 2^50 by under 2^-1.3
+      uint64_t w = __builtin_bit_cast(uint64_t, c + (c < b - 0.5 ? (kTwo52 - b) + q : kTwo52 - b)) - kTwo52Bits;
+      computed_here(w);
+      res.w[im][r % 8] = w;
+    }
+    stage_fence();
+    if (r == 7) store_half<LOGN>(row, res, 0);
+  }
+}
+
+// All rows of the current item (its samples are drawn and v transformed).
+template <int LOGN, int RC, bool BRIGHT>
+__device__ __forceinline__ void encrypt_rows(int L, const double (&v)[1][2][16], double *lds, const Samples<LOGN> &smp,
+                                             int B, double fv, double fb, uint64_t *out, const LimbConsts &lc,
+                                             const DevTables &dt) {
+  constexpr int N = 1 << LOGN;
+  KeyPart first = load_part<LOGN>(key_row<LOGN>(0, 0, L, dt), 0);
+  RowHalf res;
+  uint64_t *before = nullptr;
+#pragma unroll 1
+  for (int l = 0; l < L; l++) {
+    uint64_t *row0 = out + (size_t)l * N, *row1 = out + ((size_t)L + l) * N;
+    encrypt_row<LOGN, RC, 0, BRIGHT>(res, before, row0, first, l, L, v, lds, smp, B, fv, fb, lc, dt);
+    first = load_part<LOGN>(key_row<LOGN>(1, l, L, dt), 0);
+    encrypt_row<LOGN, RC, 1, BRIGHT>(res, row0, row1, first, l, L, v, lds, smp, B, fv, fb, lc, dt);
+    before = row1;
+    first = load_part<LOGN>(key_row<LOGN>(0, l + 1 < L ? l + 1 : l, L, dt), 0);
+  }
+  store_half<LOGN>(before, res, 1);
+}
+
+// Bound by VALU issue and, nearly as much, by LDS stores: 65,536 encryptions at N = 8192 and 4 primes
+// take 17.2 ms (3.8 M ciphertexts/s, 2 TB/s of stores) where 12 prime-field transforms took 23.7.
+// About 2 ms of it are the samples, 1.5 the keys' loads and the stores.  Registers are budgeted for
+// two waves per SIMD, that is two 256-thread workgroups per CU, of which one computes while the
+// other waits; v_hat stays in 64 of them through all rows (reloaded for each row it took 20.8 ms).
+// Other rings, 65,536 ciphertexts, before and now: N = 4096 7.26 and 6.36, N = 2048 3.31 and 3.00,
+// N = 16384 92.6 and 68.9 ms.
+template <int LOGN, int RC, int MODE, bool BRIGHT>
+__global__ void __launch_bounds__(1 << (LOGN - 5)) __attribute__((amdgpu_waves_per_eu(2)))
+    k_encrypt(EncJob job, const LimbConsts *__restrict__ lcp, DevTables dt) {
+  constexpr int N = 1 << LOGN;
+  const LimbConsts &lc = *lcp;
+  extern __shared__ __attribute__((aligned(128))) double lds[];
+  const int L = lc.L, B = lc.B;
+  const uint64_t count = enc_count<MODE>(job);
+  for (uint64_t it = blockIdx.x; it < count; it += gridDim.x) {
+    const EncItem e = enc_item<MODE, BRIGHT>(job, it, lc);
+    Samples<LOGN> smp;
+    draw_item<LOGN>(smp, lds, B, job.seed0, job.seed1, e.t, Fft<LOGN>::T, true, true, dt);
+    double v[1][2][16];
+    encrypt_forward<LOGN>(v, lds, smp, dt);
+    encrypt_rows<LOGN, RC, BRIGHT>(L, v, lds, smp, B, e.fv, e.fb, job.out + e.slot * (uint64_t)(2 * L) * N, lc, dt);
+  }
+}
+
+// The same for so few pixels that whole ciphertexts leave the device part empty: workgroup (i, p)
+// encrypts rows p 2L/P..(p+1) 2L/P-1 of pixel i, P = gridDim.y (row w: polynomial w / L of limb w
+// mod L).  Each draws the samples its rows need with all its threads, of which the first T stay
+// for the transforms.
+template <int LOGN, int RC, int MODE, bool BRIGHT>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+    k_encrypt_few(EncJob job, const LimbConsts *__restrict__ lcp, DevTables dt) {
+  constexpr int N = 1 << LOGN;
+  const LimbConsts &lc = *lcp;
+  extern __shared__ __attribute__((aligned(128))) double lds[];
+  const int L = lc.L, B = lc.B, item = (int)blockIdx.x, part = (int)blockIdx.y, parts = (int)gridDim.y;
+  const int w0 = 2 * L * part / parts, w1 = 2 * L * (part + 1) / parts;
+  if ((uint64_t)item >= enc_count<MODE>(job)) return;
+  const EncItem e = enc_item<MODE, BRIGHT>(job, (uint64_t)item, lc);
+  Samples<LOGN> smp;
+  draw_item<LOGN>(smp, lds, B, job.seed0, job.seed1, e.t, (int)blockDim.x, w0 < L, w1 > L, dt);
+  if (threadIdx.x >= Fft<LOGN>::T) return;  // whole waves: the barriers below are among the remaining ones
+  double v[1][2][16];
+  encrypt_forward<LOGN>(v, lds, smp, dt);
+  uint64_t *out = job.out + e.slot * (uint64_t)(2 * L) * N, *before = nullptr;
+  RowHalf res;
+#pragma unroll 1
+  for (int w = w0; w < w1; w++) {
+    const int p = w >= L, l = p ? w - L : w;
+    uint64_t *row = out + (size_t)w * N;
+    const KeyPart first = load_part<LOGN>(key_row<LOGN>(p, l, L, dt), 0);
+    if (p == 0)
+      encrypt_row<LOGN, RC, 0, BRIGHT>(res, before, row, first, l, L, v, lds, smp, B, e.fv, e.fb, lc, dt);
+    else
+      encrypt_row<LOGN, RC, 1, BRIGHT>(res, before, row, first, l, L, v, lds, smp, B, e.fv, e.fb, lc, dt);
+    before = row;
+  }
+  store_half<LOGN>(before, res, 1);
+}
+
+// ---------------------------------------------------------------------------
+// The same through prime-field transforms, for N = 2^11 and 2^12: x = NTT(v) per limb, c0 =
+// INTT(x pk0^) + e0 + m, c1 = INTT(x pk1^) + e1.  N/8 threads per ciphertext where the complex
+// transforms have N/32, so it has the lower latency where whole ciphertexts just fill the device
+// (RingLaunch::encrypt).
+// ---------------------------------------------------------------------------
+template <int LOGN>
+constexpr bool kEncryptNtt = LOGN <= 12;
+
+// One limb of the encryption of the current item, by the whole workgroup (the samples are drawn).
+template <int LOGN, int LOGR, int RC, bool BRIGHT>
+__device__ __forceinline__ void encrypt_limb_ntt(int l, double *lds, const uint16_t *smpl, int L, int B, double fv,
+                                                 double fb, uint64_t *out, const LimbConsts &lc, const DevTables &dt) {
   using S = Shape<LOGN, LOGR>;
   using Red = Schedule<LOGN, RC>;
   constexpr int N = S::N, R = S::R, T = S::T;
   const double q = lc.q[l], qinv = lc.qinv[l];
   const int tid = opaque(threadIdx.x);
-  auto sample = [&](int r) -> uint32_t {
-    if constexpr (S::kSmpLds)
-      return (uint32_t)smpl[tid + T * r];
-    else
-      return smp[r];
-  };
+  auto sample = [&](int r) { return (uint32_t)smpl[tid + T * r]; };
   double x[R];
 #pragma unroll
   for (int r = 0; r < R; r++) x[r] = (double)smp_t(sample(r));
@@ -120,103 +431,59 @@ __device__ __forceinline__ void encrypt_limb(int l, double *lds, const uint16_t 
   // both pointwise products at once (one wait for the key loads; x is then dead and
   // the second product takes its registers through the first inverse transform)
   double y[R], y1[R];
-  {
-    const double *pk0 = dt.pk_hat + (size_t)l * N, *pk1 = dt.pk_hat + ((size_t)L + l) * N;
+  const double *pk0 = dt.pk_hat + (size_t)l * N, *pk1 = dt.pk_hat + ((size_t)L + l) * N;
 #pragma unroll
-    for (int r = 0; r < R; r++) {
-      const unsigned e = elem_index<LOGN, LOGR, S::LAST>(tid, r);
-      y[r] = mulmod(x[r], ld_table(pk0, e), q, qinv);
-      y1[r] = mulmod(x[r], ld_table(pk1, e), q, qinv);
-    }
+  for (int r = 0; r < R; r++) {
+    const unsigned e = elem_index<LOGN, LOGR, S::LAST>(tid, r);
+    y[r] = mulmod(x[r], ld_table(pk0, e), q, qinv);
+    y1[r] = mulmod(x[r], ld_table(pk1, e), q, qinv);
   }
-  if constexpr (S::kDual) {
-    // c0 and c1 of this limb through one paired inverse transform; the plaintext and
-    // e0 are loaded before its final exchange
-    double add[R];
-    ntt_inverse2<LOGN, LOGR, Red::inv>(y, y1, lds, lds + S::SLOTS + kCdtSlots + 64, tid, dt.tw_inv + (size_t)l * N,
-                                       q, qinv, [&] {
-#pragma unroll
-      for (int r = 0; r < R; r++) {
-        const int j = tid + T * r;
-        add[r] = (double)smp_g(sample(r), kSmpShiftG2, B) + __builtin_rint(value * ld_table(dt.enc_T, j));
-        if (BRIGHT) add[r] += __builtin_rint(fb * ld_table(dt.cosj, j));
-      }
-    });
-    uint64_t *dst0 = out + (size_t)l * N, *dst1 = out + ((size_t)L + l) * N;
+  // c0 and c1 of this limb through one paired inverse transform; the plaintext and
+  // e0 are loaded before its final exchange
+  double add[R];
+  ntt_inverse2<LOGN, LOGR, Red::inv>(y, y1, lds, lds + S::SLOTS + kCdtSlots + 64, tid, dt.tw_inv + (size_t)l * N, q,
+                                     qinv, [&] {
 #pragma unroll
     for (int r = 0; r < R; r++) {
-      const unsigned c = tid + T * r;
-      const double v0 = canon(y[r] + add[r], q, qinv);
-      const double v1 = canon(y1[r] + (double)smp_g(sample(r), kSmpShiftG3, B), q, qinv);
-      __builtin_nontemporal_store(f64_to_u64(v0), word_at(dst0, c));
-      __builtin_nontemporal_store(f64_to_u64(v1), word_at(dst1, c));
-      if constexpr (KEEP) {
-        k0[r] = v0;
-        k1[r] = v1;
-      }
+      const double cs = ld_table(dt.cosj, tid + T * r);
+      add[r] = (double)smp_g(sample(r), kSmpShiftG2, B) + __builtin_rint(fv * cs);
+      if (BRIGHT) add[r] += __builtin_rint(fb * cs);
     }
-    return;
-  }
-#pragma unroll 1
-  for (int poly = 0; poly < 2; poly++) {
-    if (poly == 1) {
+  });
+  uint64_t *dst0 = out + (size_t)l * N, *dst1 = out + ((size_t)L + l) * N;
 #pragma unroll
-      for (int r = 0; r < R; r++) y[r] = y1[r];
-    }
-    // the plaintext (poly 0) and the Gaussian term, loaded before the final exchange
-    double add[R];
-    ntt_inverse<LOGN, LOGR, Red::inv>(y, lds, tid, dt.tw_inv + (size_t)l * N, q, qinv, [&] {
-#pragma unroll
-      for (int r = 0; r < R; r++) {
-        const int j = tid + T * r;
-        add[r] = (double)smp_g(sample(r), poly == 0 ? kSmpShiftG2 : kSmpShiftG3, B);
-        if (poly == 0) {
-          add[r] += __builtin_rint(value * ld_table(dt.enc_T, j));
-          if (BRIGHT) add[r] += __builtin_rint(fb * ld_table(dt.cosj, j));
-        }
-      }
-    });
-    uint64_t *dst = out + ((size_t)poly * L + l) * N;
-#pragma unroll
-    for (int r = 0; r < R; r++) {
-      const double v = canon(y[r] + add[r], q, qinv);
-      __builtin_nontemporal_store(f64_to_u64(v), word_at(dst, tid + T * r));
-      if constexpr (KEEP) (poly == 0 ? k0 : k1)[r] = v;
-    }
+  for (int r = 0; r < R; r++) {
+    const unsigned c = tid + T * r;
+    const double v0 = canon(y[r] + add[r], q, qinv);
+    const double v1 = canon(y1[r] + (double)smp_g(sample(r), kSmpShiftG3, B), q, qinv);
+    __builtin_nontemporal_store(f64_to_u64(v0), word_at(dst0, c));
+    __builtin_nontemporal_store(f64_to_u64(v1), word_at(dst1, c));
   }
 }
 
 template <int LOGN, int LOGR, int RC, int MODE, bool BRIGHT>
 __global__ void __launch_bounds__(1 << (LOGN - LOGR))
-    k_encrypt(EncJob job, const LimbConsts *__restrict__ lcp, DevTables dt) {
+    k_encrypt_ntt(EncJob job, const LimbConsts *__restrict__ lcp, DevTables dt) {
   using S = Shape<LOGN, LOGR>;
-  constexpr int N = S::N, R = S::R, T = S::T;
+  constexpr int N = S::N, T = S::T;
   const LimbConsts &lc = *lcp;
-  extern __shared__ double lds[];
+  extern __shared__ __attribute__((aligned(128))) double lds[];
   uint64_t *cdt = reinterpret_cast<uint64_t *>(lds + S::SLOTS);
-  uint16_t *lds16 = reinterpret_cast<uint16_t *>(lds);
-  uint16_t *smpl = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(lds) + S::enc_base_bytes);
+  uint16_t *smpl = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(lds) + S::enc_smp_at);
+  uint8_t *guide = reinterpret_cast<uint8_t *>(lds) + S::enc_guide_at;
   const int tid = threadIdx.x;
   for (int i = tid; i < kCdtSlots; i += T) cdt[i] = dt.cdt[i];
+  for (int i = tid; i < (1 << kGuideBits) / 8; i += T) reinterpret_cast<uint64_t *>(guide)[i] = dt.cdt[kCdtSlots + i];
   const int L = lc.L, B = lc.B;
-  uint64_t count = job.n;
-  if (MODE == kEncList || (MODE == kEncEntries && job.list_count)) count = *job.list_count;
+  const uint64_t count = enc_count<MODE>(job);
   for (uint64_t it = blockIdx.x; it < count; it += gridDim.x) {
-    const uint64_t item = MODE == kEncList ? (uint64_t)job.list[it] : it;
-    const uint64_t t = MODE == kEncEntries ? job.ts[item] : job.first_index + item;
-    const double value = MODE == kEncEntries ? (double)job.vals[item] : (double)job.px[item];
-    const double fb =
-        BRIGHT ? job.seg_b[segment_of(job.seg_end, job.n_seg, job.seg_base + item)] * job.bright_scale : 0.0;
-    uint64_t *out = job.out + item * (uint64_t)(2 * L) * N;
+    const EncItem e = enc_item<MODE, BRIGHT>(job, it, lc);
     __syncthreads();
-    uint32_t smp[R];  // used when the samples stay in registers
-    if constexpr (S::kSmpLds)
-      draw_samples<LOGN, LOGR>(smpl, cdt, B, opaque(tid), job.seed0, job.seed1, t, kTagV, kTagE0, kTagE1);
-    else
-      draw_samples<LOGN, LOGR>(smp, lds16, cdt, B, opaque(tid), job.seed0, job.seed1, t, kTagV, kTagE0, kTagE1);
-    double unused0[R], unused1[R];
+    draw_samples<LOGN, true>(smpl, cdt, B, opaque(tid), T, job.seed0, job.seed1, e.t, kTagV, kTagE0, kTagE1, true, true,
+                             guide);
     for (int l = 0; l < L; l++)
-      encrypt_limb<LOGN, LOGR, RC, BRIGHT, false>(l, lds, smpl, smp, L, B, value, fb, out, lc, dt, unused0, unused1);
+      encrypt_limb_ntt<LOGN, LOGR, RC, BRIGHT>(l, lds, smpl, L, B, e.fv, e.fb, job.out + e.slot * (uint64_t)(2 * L) * N,
+                                               lc, dt);
   }
 }
 
@@ -230,7 +497,7 @@ __global__ void __launch_bounds__(1 << (LOGN - LOGR))
   using Red = Schedule<LOGN, RC>;
   constexpr int N = S::N, R = S::R, T = S::T;
   const LimbConsts &lc = *lcp;
-  extern __shared__ double lds[];
+  extern __shared__ __attribute__((aligned(128))) double lds[];
   uint64_t *cdt = reinterpret_cast<uint64_t *>(lds + S::SLOTS);
   uint16_t *lds16 = reinterpret_cast<uint16_t *>(lds);
   const int tid = threadIdx.x;
@@ -290,17 +557,51 @@ __global__ void __launch_bounds__(1 << (LOGN - LOGR))
 }
 
 // ---------------------------------------------------------------------------
-// NTT-domain key copies used by encryption and decryption:
-//   blockIdx.y = 0: s_hat_l * N^-1;  1: pk0_hat_l * N^-1;  2: pk1_hat_l * N^-1
+// Complex transforms of the keys, times 1/M (fft.hpp), value r of thread tid at r T + tid:
+// blockIdx.x = 0: s; 1 + p L + l: the low and high pieces of pk_p in limb l (centered residues).
 // ---------------------------------------------------------------------------
+template <int LOGN, int RC>
+__global__ void __launch_bounds__(1 << (LOGN - 5)) k_keys_prepare(const LimbConsts *__restrict__ lcp, DevTables dt) {
+  using F = Fft<LOGN>;
+  constexpr double unit = Split<RC>::unit;
+  const LimbConsts &lc = *lcp;
+  extern __shared__ __attribute__((aligned(128))) double lds[];
+  const int tid = threadIdx.x, p = (int)fft_place<LOGN>((unsigned)tid), L = lc.L, row = (int)blockIdx.x - 1;
+  double x[2][2][16];
+#pragma unroll
+  for (int r = 0; r < 32; r++) {
+    const int j = p + F::T * r;
+    double lo, hi = 0.0;
+    if (row < 0) {
+      lo = (double)dt.s[j];
+    } else {
+      const double q = lc.q[row % L], w = (double)dt.pk[(size_t)row * 2 * F::M + j];
+      const double c = w > 0.5 * q ? w - q : w;
+      hi = __builtin_rint(c * (1.0 / unit));
+      lo = __builtin_fma(-hi, unit, c);
+    }
+    x[0][r >> 4][r & 15] = lo;
+    x[1][r >> 4][r & 15] = hi;
+  }
+  fft_forward<LOGN, 2>(x, lds, tid, dt.fft_fwd);
+  Cplx *dst = row < 0 ? dt.s_fft : dt.pk_fft + (size_t)row * 2 * F::M;
+#pragma unroll
+  for (int r = 0; r < 16; r++) {
+    const int at = r * F::T + tid;
+    dst[at] = Cplx{x[0][0][r] * (1.0 / F::M), x[0][1][r] * (1.0 / F::M)};
+    if (row >= 0) dst[F::M + at] = Cplx{x[1][0][r] * (1.0 / F::M), x[1][1][r] * (1.0 / F::M)};
+  }
+}
+
+// Prime-field transforms of the keys in limb l = blockIdx.x, times N^-1: blockIdx.y = 0: s; 1, 2: pk0,
+// pk1 (for k_encrypt_ntt).
 template <int LOGN, int LOGR, int RC>
-__global__ void __launch_bounds__(1 << (LOGN - LOGR))
-    k_keys_prepare(const LimbConsts *__restrict__ lcp, DevTables dt) {
+__global__ void __launch_bounds__(1 << (LOGN - LOGR)) k_keys_prepare_ntt(const LimbConsts *__restrict__ lcp, DevTables dt) {
   using S = Shape<LOGN, LOGR>;
   using Red = Schedule<LOGN, RC>;
   constexpr int N = S::N, R = S::R, T = S::T;
   const LimbConsts &lc = *lcp;
-  extern __shared__ double lds[];
+  extern __shared__ __attribute__((aligned(128))) double lds[];
   const int tid = threadIdx.x, l = blockIdx.x, which = blockIdx.y, L = lc.L;
   const double q = lc.q[l], qinv = lc.qinv[l];
   double x[R];
@@ -323,7 +624,7 @@ __global__ void __launch_bounds__(1 << (LOGN - LOGR))
 // ---------------------------------------------------------------------------
 // launch helpers for one ring degree
 // ---------------------------------------------------------------------------
-template <int LOGN, int LOGR, auto KERNEL, size_t BYTES = Shape<LOGN, LOGR>::lds_bytes>
+template <auto KERNEL, size_t BYTES>
 static hipError_t set_lds() {
   // once per kernel and device (also keeps the call out of graph captures after the first launch)
   static std::atomic<uint64_t> done{0};
@@ -345,35 +646,92 @@ static hipError_t set_lds() {
 
 namespace ckks {
 
+// Kernels on complex transforms.
+template <int LOGN, int RC>
+struct FftLaunch {
+  static constexpr int T = Fft<LOGN>::T;
+  using B = FftLds<LOGN>;
+  template <int MODE, bool BRIGHT>
+  static hipError_t encrypt_as(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {
+    hipError_t e = set_lds<k_encrypt<LOGN, RC, MODE, BRIGHT>, B::encrypt>();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_encrypt<LOGN, RC, MODE, BRIGHT>), dim3((uint32_t)grid), dim3(T), B::encrypt, st, job, c->d_lc,
+                       c->dev);
+    return hipGetLastError();
+  }
+  // Workgroups as large as still leave two parts per pixel resident (8 waves per CU), then as many
+  // parts as are: threads for the samples first, since every part draws them again (64 pixels at N
+  // = 8192: 4 parts of 512 threads 42.6 us, 8 of 256 51.2).
+  template <int MODE, bool BRIGHT>
+  static hipError_t encrypt_few(const ckks_ctx *c, const EncJob &job, hipStream_t st) {
+    hipError_t e = set_lds<k_encrypt_few<LOGN, RC, MODE, BRIGHT>, B::encrypt>();
+    if (e != hipSuccess) return e;
+    const uint64_t lanes = 512 * (uint64_t)c->num_cus;
+    int threads = 512;
+    while (threads > T && 2 * job.n * threads > lanes) threads /= 2;
+    const uint64_t parts = std::min<uint64_t>(2 * c->lc.L, std::max<uint64_t>(1, lanes / threads / job.n));
+    hipLaunchKernelGGL((k_encrypt_few<LOGN, RC, MODE, BRIGHT>), dim3((uint32_t)job.n, (uint32_t)parts), dim3(threads),
+                       B::encrypt, st, job, c->d_lc, c->dev);
+    return hipGetLastError();
+  }
+  static hipError_t prepare(const ckks_ctx *c, hipStream_t st) {
+    hipError_t e = set_lds<k_keys_prepare<LOGN, RC>, B::exchange>();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_keys_prepare<LOGN, RC>), dim3(2 * c->lc.L + 1), dim3(T), B::exchange, st, c->d_lc, c->dev);
+    using S = Shape<LOGN, 4>;
+    e = set_lds<k_keys_prepare_ntt<LOGN, 4, RC>, S::lds_bytes>();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_keys_prepare_ntt<LOGN, 4, RC>), dim3(c->lc.L, c->dev.pk_hat ? 3 : 1), dim3(S::T), S::lds_bytes,
+                       st, c->d_lc, c->dev);
+    return hipGetLastError();
+  }
+  template <int LIMBS>
+  static hipError_t decrypt_as(const ckks_ctx *c, const DecJob &job, uint64_t grid, hipStream_t st) {
+    hipError_t e = set_lds<k_decrypt<LOGN, RC, LIMBS>, B::exchange>();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_decrypt<LOGN, RC, LIMBS>), dim3((uint32_t)grid), dim3(T), B::exchange, st, job, c->d_lc,
+                       c->dev);
+    return hipGetLastError();
+  }
+  static hipError_t decrypt(const ckks_ctx *c, const DecJob &job, int limbs, uint64_t grid, hipStream_t st) {
+    return limbs == 2 ? decrypt_as<2>(c, job, grid, st) : decrypt_as<1>(c, job, grid, st);
+  }
+};
+
+// Kernels on prime-field transforms.
 template <int LOGN, int LOGR, int RC>
 struct Launch {
   using S = Shape<LOGN, LOGR>;
+  static hipError_t keygen(const ckks_ctx *c, uint64_t s0, uint64_t s1, hipStream_t st) {
+    hipError_t e = set_lds<k_keygen<LOGN, LOGR, RC>, S::lds_bytes>();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_keygen<LOGN, LOGR, RC>), dim3(c->lc.L), dim3(S::T), S::lds_bytes, st, s0, s1, c->d_lc, c->dev);
+    return hipGetLastError();
+  }
   template <int MODE, bool BRIGHT>
   static hipError_t encrypt_as(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {
-    hipError_t e = set_lds<LOGN, LOGR, k_encrypt<LOGN, LOGR, RC, MODE, BRIGHT>, S::enc_lds_bytes>();
+    hipError_t e = set_lds<k_encrypt_ntt<LOGN, LOGR, RC, MODE, BRIGHT>, S::enc_lds_bytes>();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_encrypt<LOGN, LOGR, RC, MODE, BRIGHT>), dim3((uint32_t)grid), dim3(S::T), S::enc_lds_bytes,
+    hipLaunchKernelGGL((k_encrypt_ntt<LOGN, LOGR, RC, MODE, BRIGHT>), dim3((uint32_t)grid), dim3(S::T), S::enc_lds_bytes,
                        st, job, c->d_lc, c->dev);
     return hipGetLastError();
   }
-  static hipError_t encrypt(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {
-    const bool bright = job.seg_b != nullptr;
-    if (job.vals || job.ts) {
-      if (!job.vals || !job.ts || bright) return hipErrorInvalidValue;
-      return encrypt_as<kEncEntries, false>(c, job, grid, st);
-    }
-    if (job.list) {
-      if (!job.list_count) return hipErrorInvalidValue;
-      return bright ? encrypt_as<kEncList, true>(c, job, grid, st) : encrypt_as<kEncList, false>(c, job, grid, st);
-    }
-    if (job.list_count) return hipErrorInvalidValue;
-    return bright ? encrypt_as<kEncPixels, true>(c, job, grid, st) : encrypt_as<kEncPixels, false>(c, job, grid, st);
+  template <int LIMBS>
+  static hipError_t decrypt_as(const ckks_ctx *c, const DecJob &job, uint64_t grid, hipStream_t st) {
+    hipError_t e = set_lds<k_decrypt_ntt<LOGN, LOGR, RC, LIMBS>, S::lds_bytes>();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_decrypt_ntt<LOGN, LOGR, RC, LIMBS>), dim3((uint32_t)grid), dim3(S::T), S::lds_bytes, st, job,
+                       c->d_lc, c->dev);
+    return hipGetLastError();
   }
-  template <bool BRIGHT, bool DECRYPT, bool MISSES>
+  static hipError_t decrypt(const ckks_ctx *c, const DecJob &job, int limbs, uint64_t grid, hipStream_t st) {
+    return limbs == 2 ? decrypt_as<2>(c, job, grid, st) : decrypt_as<1>(c, job, grid, st);
+  }
+  template <bool DECRYPT>
   static hipError_t fused_as(const ckks_ctx *c, const FusedJob &job, hipStream_t st) {
-    constexpr auto kernel = k_cached_fused<LOGN, LOGR, RC, BRIGHT, DECRYPT, MISSES>;
-    constexpr size_t lds = MISSES ? S::enc_lds_bytes : DECRYPT ? S::lds_bytes : 0;
-    hipError_t e = set_lds<LOGN, LOGR, kernel, lds>();
+    constexpr auto kernel = k_hits_fused<LOGN, LOGR, RC, DECRYPT>;
+    constexpr size_t lds = DECRYPT ? S::lds_bytes : 0;
+    hipError_t e = set_lds<kernel, lds>();
     if (e != hipSuccess) return e;
     // a persistent grid: the workgroups that fit on the device at once
     static std::atomic<int> resident{0};
@@ -394,46 +752,26 @@ struct Launch {
       if (!jb.dec_out) return hipErrorInvalidValue;
       if (grid > jb.ring) grid = jb.ring;
     }
-    if (!jb.cursor) return hipErrorInvalidValue;
     e = launch_fill_u32(jb.cursor, kXcds, 0u, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_cached_fused<LOGN, LOGR, RC, BRIGHT, DECRYPT, MISSES>), dim3((uint32_t)grid), dim3(S::T), lds,
-                       st, jb, c->d_lc, c->dev);
+    hipLaunchKernelGGL((k_hits_fused<LOGN, LOGR, RC, DECRYPT>), dim3((uint32_t)grid), dim3(S::T), lds, st, jb, c->d_lc,
+                       c->dev);
     return hipGetLastError();
   }
-  // misses: false when the job's cache holds every value (no pixel is encrypted in full)
-  static hipError_t fused(const ckks_ctx *c, const FusedJob &job, bool misses, hipStream_t st) {
+  static hipError_t fused(const ckks_ctx *c, const FusedJob &job, hipStream_t st) {
     if (job.n == 0) return hipSuccess;
-    const bool bright = job.seg_b != nullptr, dec = job.dec_out != nullptr;
-    if (!misses) {
-      if (!job.counters) return hipErrorInvalidValue;
-      if (bright) return dec ? fused_as<true, true, false>(c, job, st) : fused_as<true, false, false>(c, job, st);
-      return dec ? fused_as<false, true, false>(c, job, st) : fused_as<false, false, false>(c, job, st);
-    }
-    if (bright) return dec ? fused_as<true, true, true>(c, job, st) : fused_as<true, false, true>(c, job, st);
-    return dec ? fused_as<false, true, true>(c, job, st) : fused_as<false, false, true>(c, job, st);
-  }
-  static hipError_t keygen(const ckks_ctx *c, uint64_t s0, uint64_t s1, hipStream_t st) {
-    hipError_t e = set_lds<LOGN, LOGR, k_keygen<LOGN, LOGR, RC>>();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_keygen<LOGN, LOGR, RC>), dim3(c->lc.L), dim3(S::T), S::lds_bytes, st, s0, s1, c->d_lc, c->dev);
-    return hipGetLastError();
-  }
-  static hipError_t prepare(const ckks_ctx *c, hipStream_t st) {
-    hipError_t e = set_lds<LOGN, LOGR, k_keys_prepare<LOGN, LOGR, RC>>();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_keys_prepare<LOGN, LOGR, RC>), dim3(c->lc.L, 3), dim3(S::T), S::lds_bytes, st, c->d_lc, c->dev);
-    return hipGetLastError();
+    if (!job.counters || !job.cursor || !job.seg_b) return hipErrorInvalidValue;
+    return job.dec_out ? fused_as<true>(c, job, st) : fused_as<false>(c, job, st);
   }
   static hipError_t relin_keygen(const ckks_ctx *c, uint64_t s0, uint64_t s1, hipStream_t st) {
-    hipError_t e = set_lds<LOGN, LOGR, k_relin_keygen<LOGN, LOGR, RC>>();
+    hipError_t e = set_lds<k_relin_keygen<LOGN, LOGR, RC>, S::lds_bytes>();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_relin_keygen<LOGN, LOGR, RC>), dim3(c->lc.L, c->lc.L + 1), dim3(S::T), S::lds_bytes, st, s0,
                        s1, c->d_lc, c->dev);
     return hipGetLastError();
   }
   static hipError_t relin_prepare(const ckks_ctx *c, hipStream_t st) {
-    hipError_t e = set_lds<LOGN, LOGR, k_relin_prepare<LOGN, LOGR, RC>>();
+    hipError_t e = set_lds<k_relin_prepare<LOGN, LOGR, RC>, S::lds_bytes>();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_relin_prepare<LOGN, LOGR, RC>), dim3(c->lc.L, c->lc.L + 1, 2), dim3(S::T), S::lds_bytes, st,
                        c->d_lc, c->dev);
@@ -441,36 +779,23 @@ struct Launch {
   }
   static hipError_t mul(const ckks_ctx *c, const uint64_t *a, const uint64_t *b, uint64_t *out, uint64_t n, int level,
                         uint64_t *scratch, hipStream_t st) {
-    hipError_t e = set_lds<LOGN, LOGR, k_mul<LOGN, LOGR, RC>>();
+    hipError_t e = set_lds<k_mul<LOGN, LOGR, RC>, S::lds_bytes>();
     if (e != hipSuccess) return e;
     const uint64_t grid = n < kMulGroups ? n : kMulGroups;
     hipLaunchKernelGGL((k_mul<LOGN, LOGR, RC>), dim3((uint32_t)grid), dim3(S::T), S::lds_bytes, st, a, b, out, n, level,
                        scratch, c->d_lc, c->dev);
     return hipGetLastError();
   }
-  template <int LIMBS>
-  static hipError_t decrypt_as(const ckks_ctx *c, const uint64_t *cts, uint64_t n, int level, double scale,
-                               double *out, hipStream_t st, uint64_t max_grid) {
-    hipError_t e = set_lds<LOGN, LOGR, k_decrypt<LOGN, LOGR, RC, LIMBS>>();
-    if (e != hipSuccess) return e;
-    uint64_t grid = n < (1u << 20) ? n : (1u << 20);
-    if (max_grid && grid > max_grid) grid = max_grid;
-    hipLaunchKernelGGL((k_decrypt<LOGN, LOGR, RC, LIMBS>), dim3((uint32_t)grid), dim3(S::T), S::lds_bytes, st, cts, n,
-                       level, 1.0 / scale, out, c->d_lc, c->dev);
-    return hipGetLastError();
-  }
-  static hipError_t decrypt(const ckks_ctx *c, const uint64_t *cts, uint64_t n, int level, double scale, double *out,
-                            int limbs, hipStream_t st, uint64_t max_grid) {
-    if (limbs == 2 && level >= 2) return decrypt_as<2>(c, cts, n, level, scale, out, st, max_grid);
-    if (limbs != 1) return hipErrorInvalidValue;
-    return decrypt_as<1>(c, cts, n, level, scale, out, st, max_grid);
-  }
 };
 
-// All launchers of one ring degree, selecting the thread shape (c->logr) and the
-// reduction class (c->rc) at run time.
+// All launchers of one ring degree, selecting the thread shape (where there is a choice) and the
+// class of the primes (c->rc) at run time.
 template <int LOGN>
 struct RingLaunch {
+  template <typename F>
+  static hipError_t pick(const ckks_ctx *c, F f) {
+    return c->rc ? f(FftLaunch<LOGN, 1>{}) : f(FftLaunch<LOGN, 0>{});
+  }
   template <typename F>
   static hipError_t pick(const ckks_ctx *c, int logr, F f) {
     if constexpr (LOGN - 3 <= 10) {  // 8 values per thread: N/8 threads, at most 1024
@@ -479,6 +804,37 @@ struct RingLaunch {
     if (logr == 4) return c->rc ? f(Launch<LOGN, 4, 1>{}) : f(Launch<LOGN, 4, 0>{});
     if (logr == 5) return c->rc ? f(Launch<LOGN, 5, 1>{}) : f(Launch<LOGN, 5, 0>{});
     return hipErrorInvalidValue;
+  }
+  // Which encryption kernel takes a job (of a list: by its largest length).  In us for n pixels, split / prime-field / whole
+  // ciphertexts by complex transforms:
+  //   N = 2048:   n = 64: 24 / 26 / 66   200: 35 / 27 / 66   3,200: - / 172 / 187   10,000: - / 538 / 504
+  //   N = 4096:   n = 128: 38 / 39 / 71  200: 54 / 41 / 71   400: 75 / 65 / 95      800: - / 118 / 108
+  //   N = 8192:   n = 64: 43 / 92 / 103  128: 66 / 95 / 102  200: 98 / 99 / 103     400: - / 186 / 149
+  //   N = 16384:  n = 64: 110 / 340 / 240  128: 180 / 350 / 265   200: - / 357 / 272
+  template <int MODE, bool BRIGHT>
+  static hipError_t encrypt_as(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {
+    const uint64_t cus = (uint64_t)c->num_cus, n = job.n;
+    constexpr uint64_t few_of[4] = {1, 2, 4, 2};  // up to this many pixels per 4 CUs
+    if (n && n <= grid && 4 * n <= few_of[LOGN - 11] * cus)
+      return pick(c, [&](auto L) { return decltype(L)::template encrypt_few<MODE, BRIGHT>(c, job, st); });
+    if constexpr (kEncryptNtt<LOGN>)
+      if (n < (LOGN == 11 ? 32 : 2) * cus)
+        return pick(c, c->logr_enc,
+                    [&](auto L) { return decltype(L)::template encrypt_as<MODE, BRIGHT>(c, job, grid, st); });
+    return pick(c, [&](auto L) { return decltype(L)::template encrypt_as<MODE, BRIGHT>(c, job, grid, st); });
+  }
+  static hipError_t encrypt(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {
+    const bool bright = job.seg_b != nullptr;
+    if (job.vals || job.ts) {
+      if (!job.vals || !job.ts || bright) return hipErrorInvalidValue;
+      return encrypt_as<kEncEntries, false>(c, job, grid, st);
+    }
+    if (job.list) {
+      if (!job.list_count) return hipErrorInvalidValue;
+      return bright ? encrypt_as<kEncList, true>(c, job, grid, st) : encrypt_as<kEncList, false>(c, job, grid, st);
+    }
+    if (job.list_count) return hipErrorInvalidValue;
+    return bright ? encrypt_as<kEncPixels, true>(c, job, grid, st) : encrypt_as<kEncPixels, false>(c, job, grid, st);
   }
 };
 
@@ -489,19 +845,19 @@ struct RingLaunch {
 #define CKKS_DEFINE_RING_ENC(LOGN)                                                                                  \
   namespace ckks {                                                                                                  \
   hipError_t launch_encrypt_##LOGN(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {           \
-    return RingLaunch<LOGN>::pick(c, c->logr_enc, [&](auto L) { return decltype(L)::encrypt(c, job, grid, st); });  \
+    return RingLaunch<LOGN>::encrypt(c, job, grid, st);                                                             \
   }                                                                                                                 \
   hipError_t launch_keygen_##LOGN(const ckks_ctx *c, uint64_t s0, uint64_t s1, hipStream_t st) {                    \
     return RingLaunch<LOGN>::pick(c, c->logr_enc, [&](auto L) { return decltype(L)::keygen(c, s0, s1, st); });      \
   }                                                                                                                 \
   hipError_t launch_keys_prepare_##LOGN(const ckks_ctx *c, hipStream_t st) {                                        \
-    return RingLaunch<LOGN>::pick(c, c->logr_enc, [&](auto L) { return decltype(L)::prepare(c, st); });             \
+    return RingLaunch<LOGN>::pick(c, [&](auto L) { return decltype(L)::prepare(c, st); });                          \
   }                                                                                                                 \
-  hipError_t launch_decrypt_##LOGN(const ckks_ctx *c, const uint64_t *cts, uint64_t n, int level, double scale,     \
-                                   double *out, int limbs, hipStream_t st, uint64_t max_grid) {                     \
-    return RingLaunch<LOGN>::pick(c, c->logr_dec, [&](auto L) {                                                     \
-      return decltype(L)::decrypt(c, cts, n, level, scale, out, limbs, st, max_grid);                               \
-    });                                                                                                             \
+  hipError_t launch_decrypt_##LOGN(const ckks_ctx *c, const DecJob &job, int limbs, uint64_t grid, hipStream_t st) { \
+    auto run = [&](auto L) { return decltype(L)::decrypt(c, job, limbs, grid, st); };                               \
+    if constexpr (kDecryptFft<LOGN>)                                                                                \
+      if (grid > (uint64_t)c->num_cus) return RingLaunch<LOGN>::pick(c, run);                                       \
+    return RingLaunch<LOGN>::pick(c, c->logr_dec, run);                                                             \
   }                                                                                                                 \
   }
 
@@ -522,8 +878,7 @@ struct RingLaunch {
 
 #define CKKS_DEFINE_RING_FUSED(LOGN)                                                                                \
   namespace ckks {                                                                                                  \
-  hipError_t launch_cached_fused_##LOGN(const ckks_ctx *c, const FusedJob &job, bool misses, hipStream_t st) {     \
-    return RingLaunch<LOGN>::pick(c, misses ? c->logr_enc : c->logr_dec,                                            \
-                                  [&](auto L) { return decltype(L)::fused(c, job, misses, st); });                  \
+  hipError_t launch_hits_fused_##LOGN(const ckks_ctx *c, const FusedJob &job, hipStream_t st) {                     \
+    return RingLaunch<LOGN>::pick(c, c->logr_dec, [&](auto L) { return decltype(L)::fused(c, job, st); });          \
   }                                                                                                                 \
   }

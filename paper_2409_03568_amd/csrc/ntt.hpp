@@ -201,6 +201,39 @@ CKKS_HD int opaque(int v) {
 }
 
 
+// Element `lane` of a row of 16- or 8-byte values that starts at the uniform address `row`, as a
+// global access with a scalar base and a 32-bit lane offset.  The base is opaque, so that
+// the accesses of a thread to constant places of a row each take theirs into the scalar base (a
+// scalar add) and share one offset register; the compiler would otherwise add the places to
+// 64-bit vector addresses.
+#if defined(__HIP_DEVICE_COMPILE__)
+#define CKKS_GLOBAL __attribute__((address_space(1)))
+template <class V>
+__device__ __forceinline__ CKKS_GLOBAL V *row_at(V *row, unsigned lane) {
+  CKKS_GLOBAL char *p = (CKKS_GLOBAL char *)(char *)row;
+  asm volatile("" : "+s"(p));
+  return (CKKS_GLOBAL V *)(p + lane * (unsigned)sizeof(V));
+}
+template <class V>
+__device__ __forceinline__ CKKS_GLOBAL const V *row_at(const V *row, unsigned lane) {
+  const CKKS_GLOBAL char *p = (const CKKS_GLOBAL char *)(const char *)row;
+  asm volatile("" : "+s"(p));
+  return (CKKS_GLOBAL const V *)(p + lane * (unsigned)sizeof(V));
+}
+#else
+template <class V>
+CKKS_HD V *row_at(V *row, unsigned lane) { return row + lane; }
+#endif
+
+// Has v computed here (the compiler otherwise moves arithmetic down to its use, and keeps the
+// operands live meanwhile).
+template <class V>
+CKKS_HD void computed_here(V &v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(v));
+#endif
+}
+
 // Keeps the device scheduler from interleaving consecutive stages: a pass compiles to
 // one straight-line block, and hoisting later stages' loads and arithmetic over earlier
 // ones raises register pressure past what two waves per SIMD can hold.
