@@ -777,14 +777,19 @@ struct Launch {
                        c->d_lc, c->dev);
     return hipGetLastError();
   }
-  static hipError_t mul(const ckks_ctx *c, const uint64_t *a, const uint64_t *b, uint64_t *out, uint64_t n, int level,
-                        uint64_t *scratch, hipStream_t st) {
-    hipError_t e = set_lds<k_mul<LOGN, LOGR, RC>, S::lds_bytes>();
+  template <bool SQUARE>
+  static hipError_t mul_as(const ckks_ctx *c, const uint64_t *a, const uint64_t *b, uint64_t *out, uint64_t n, int level,
+                           uint64_t *scratch, hipStream_t st) {
+    hipError_t e = set_lds<k_mul<LOGN, LOGR, RC, SQUARE>, S::lds_bytes>();
     if (e != hipSuccess) return e;
     const uint64_t grid = n < kMulGroups ? n : kMulGroups;
-    hipLaunchKernelGGL((k_mul<LOGN, LOGR, RC>), dim3((uint32_t)grid), dim3(S::T), S::lds_bytes, st, a, b, out, n, level,
-                       scratch, c->d_lc, c->dev);
+    hipLaunchKernelGGL((k_mul<LOGN, LOGR, RC, SQUARE>), dim3((uint32_t)grid), dim3(S::T), S::lds_bytes, st, a, b, out, n,
+                       level, scratch, c->d_lc, c->dev);
     return hipGetLastError();
+  }
+  static hipError_t mul(const ckks_ctx *c, const uint64_t *a, const uint64_t *b, uint64_t *out, uint64_t n, int level,
+                        uint64_t *scratch, hipStream_t st) {
+    return a == b ? mul_as<true>(c, a, b, out, n, level, scratch, st) : mul_as<false>(c, a, b, out, n, level, scratch, st);
   }
 };
 

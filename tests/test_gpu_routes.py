@@ -77,3 +77,23 @@ def test_miss_lists_and_batches(P, log_n, L, bits, log_scale, n):
     assert torch.equal(out[0], out[1])
     want = px.double() + torch.tensor([2.0] + [-3.0] * (n - 1), dtype=torch.float64, device="cuda")
     assert float((out[0] - want).abs().max()) < 0.5
+
+
+@pytest.mark.parametrize("log_n,L,bits,log_scale", [r[:4] for r in ROUTES])
+@pytest.mark.parametrize("level", [1, 2, 0])
+def test_square_is_the_product(P, log_n, L, bits, log_scale, level):
+    """The product of a buffer with itself takes half the forward transforms; it equals the product
+    with a copy, also where the result replaces the factor."""
+    import torch
+
+    px = torch.arange(0, 255, 51, dtype=torch.uint8, device="cuda")
+    ctx = P.Context(log_n, L, bits, log_scale)
+    ctx.keygen((26, log_n))
+    ctx.relin_keygen((27, log_n))
+    a = ctx.encrypt_pixels(px, (28, log_n))
+    while level and a.level > level:
+        a = ctx.rescale(a)
+    b = P.Ciphertexts(a.data.clone(), a.level, a.scale)
+    want = ctx.mul(a, b).data.clone()
+    assert torch.equal(ctx.mul(a, a).data, want)
+    assert torch.equal(ctx.mul(b, b, out=b).data, want)
