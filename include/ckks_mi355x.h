@@ -146,9 +146,11 @@ int ckks_context_create(const ckks_params *params, int device, ckks_ctx **out);
 /* Wait for all work of the context and free it.  NULL is ignored. */
 void ckks_context_destroy(ckks_ctx *ctx);
 
-/* Tuning of the NTT kernels (encryption, decryption, keys, ciphertext product): each
+/* Tuning of the kernels on prime-field transforms (keys, ciphertext product, cache hits of
+ * batches, and the encryptions and decryptions that have the lower latency through them): each
  * thread of a workgroup holds values_per_thread ring coefficients (8, 16 or 32), so a
- * workgroup has N / values_per_thread threads (at most 1024: 8 needs N <= 8192).  The
+ * workgroup has N / values_per_thread threads (at most 1024: 8 needs N <= 8192).  Kernels on
+ * complex transforms (large encryptions, decryption at N = 8192) have one shape.  The
  * setter applies to all of them (ckks_autotune chooses per kernel); the getter reports
  * the encryption kernel's.  Results are identical for every setting; only speed differs.
  * CKKS_EINVAL for other values.  The default is 8 where allowed, else 16. */
@@ -339,12 +341,13 @@ int ckks_stream_sync(ckks_ctx *ctx, void *stream);
 int ckks_stream_status(ckks_ctx *ctx, void *stream);
 
 /* ---- autotuning ----
- * Times the NTT kernels (encryption, Sec. 2.2.2: one forward and two inverse
- * transforms per limb; decryption: one forward and one inverse on limb 0) at each
- * supported register blocking (8, 16 or 32 values per thread) on trial_cts synthetic
- * ciphertexts, and, once ckks_relin_keygen has run, the relinearized product
+ * Times the kernels on prime-field transforms (encryption, Sec. 2.2.2, of trial_cts
+ * pixels, but at most a few hundred; decryption on limb 0) at each supported register blocking (8,
+ * 16 or 32 values per thread) on trial_cts synthetic ciphertexts, and, once
+ * ckks_relin_keygen has run, the relinearized product
  * (Sec. 2.2.3) of trial_cts pairs; keeps the fastest width for each kernel on this
- * context.  Then times the launch shapes of the HBM-bound kernels: the row-wise
+ * context, or the present one when the fastest is not 3% faster.  Then times the
+ * launch shapes of the HBM-bound kernels: the row-wise
  * kernels (ciphertext addition, Sec. 2.2.3, standing for every row-wise kernel:
  * subtraction, constants, rescaling, radix gather) at 0 (one workgroup per row), 2, 4,
  * 8 and 16 workgroups per compute unit, and the value-cache gather (Sec. 3.2) at 2, 4,
@@ -393,18 +396,16 @@ int ckks_tune_load(ckks_ctx *ctx, const char *path, int *found);
  * chunk_cts ciphertexts owned by the plan, so device memory stays bounded whatever the
  * batch size.  The cache metadata of the whole batch comes first, so hits are grouped by
  * pool member and cache slot over all images (each pair's entries are read from L2 for
- * all its pixels); then one persistent launch assembles every ciphertext -- entry + pool
- * member for a cached value, full encryption for a miss or for every pixel without a
- * cache -- with the brightness fused in, writes it to the ring (a workgroup reuses its
- * slots in turn) and decrypts it from the registers that hold its limb-0 rows.  With a
- * VALUE_FULL cache the launch has no encryption path and needs only the decryption's LDS
- * and registers, so several workgroups share a CU.  (Where limb 0 alone does not decode
+ * all its pixels); then one persistent launch assembles every cache hit -- entry + pool
+ * member, with the brightness fused in --, writes it to the ring (a workgroup reuses its
+ * slots in turn) and decrypts it from the registers that hold its limb-0 rows.  Misses
+ * (every pixel without a cache) are encrypted with the brightness and decrypted through the
+ * ring, chunk_cts at a time.  (Where limb 0 alone does not decode
  * exactly, chunks of chunk_cts ciphertexts are produced and then decrypted from the ring
  * with the two-limb lift.)  Ciphertexts equal ckks_encrypt_cached / ckks_encrypt_pixels
  * followed by ckks_add_const, bit for bit; the decrypted values equal ckks_decrypt_pixels
- * of those ciphertexts bit for bit when the context's encryption and decryption use the
- * same NTT width (the decoded sum's rounding follows the workgroup shape), otherwise to a
- * few units in the last place.  A plan runs one batch at a time.
+ * of those ciphertexts bit for bit when decryption uses the default width (the decoded
+ * sum's rounding follows the workgroup shape), otherwise to a few units in the last place.  A plan runs one batch at a time.
  * With use_graph, the whole chunk sequence is captured once into a HIP graph and
  * replayed while ckks_batch_run is called again with the same arguments.
  */

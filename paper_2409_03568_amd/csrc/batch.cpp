@@ -369,28 +369,37 @@ int ckks_autotune(ckks_ctx *ctx, uint32_t trial_cts, ckks_tune_report *out) {
   const int keep_row = ctx->row_wgs, keep_gather = ctx->gather_wgs;
   double enc_ms[3] = {INFINITY, INFINITY, INFINITY}, dec_ms[3] = {INFINITY, INFINITY, INFINITY};
   double mul_ms[3] = {INFINITY, INFINITY, INFINITY};
+  EncJob job;
+  job.px = px;
+  job.n = trial_cts;
+  job.seed0 = 0x7u;
+  job.seed1 = 0x70u;
+  job.out = cts;
+  if (e == hipSuccess) e = launch_encrypt(ctx, job, trial_cts, nullptr);
+  // Counts for which the width matters: below two pixels per CU encryption takes the prime-field
+  // kernel where there is one, and at N = 8192 decryption does up to one workgroup per CU.
+  const uint32_t enc_cts = std::min<uint32_t>(trial_cts, 2u * (uint32_t)ctx->num_cus - 1);
+  const uint64_t dec_grid = ctx->prm.log_n == 13 ? (uint64_t)ctx->num_cus : 0;
   for (int w = 0; w < 3 && e == hipSuccess; w++) {
     if ((ctx->N >> (3 + w)) > 1024) continue;  // more threads than a workgroup holds
     ctx->logr_enc = ctx->logr_dec = ctx->logr_mul = 3 + w;
-    EncJob job;
-    job.px = px;
-    job.n = trial_cts;
-    job.seed0 = 0x7u;
-    job.seed1 = 0x70u;
-    job.out = cts;
-    enc_ms[w] = best_ms([&] { return launch_encrypt(ctx, job, trial_cts, nullptr); }, nothing);
-    dec_ms[w] = best_ms([&] { return launch_decrypt(ctx, cts, trial_cts, (int)L, ctx->scale, dec, 1, nullptr); },
-                        nothing);
+    job.n = enc_cts;
+    enc_ms[w] = best_ms([&] { return launch_encrypt(ctx, job, enc_cts, nullptr); }, nothing);
+    dec_ms[w] = best_ms(
+        [&] { return launch_decrypt(ctx, cts, trial_cts, (int)L, ctx->scale, dec, 1, nullptr, dec_grid); }, nothing);
     if (prod)
       mul_ms[w] = best_ms([&] { return launch_mul(ctx, cts, cts, prod, trial_cts, (int)L, scratch, nullptr); },
                           nothing);
   }
-  int be = 0, bd = 0, bm = 0;
-  for (int w = 1; w < 3; w++) {
-    if (enc_ms[w] < enc_ms[be]) be = w;
-    if (dec_ms[w] < dec_ms[bd]) bd = w;
-    if (mul_ms[w] < mul_ms[bm]) bm = w;
-  }
+  // another width than the present one has to be faster by more than timings differ: kernels on
+  // complex transforms have no width
+  auto fastest = [](const double (&ms)[3], int keep) {
+    int best = keep;
+    for (int w = 0; w < 3; w++)
+      if (ms[w] < (best == keep ? 0.97 : 1.0) * ms[best]) best = w;
+    return best;
+  };
+  const int be = fastest(enc_ms, keep_enc - 3), bd = fastest(dec_ms, keep_dec - 3), bm = fastest(mul_ms, keep_mul - 3);
   ctx->logr_enc = 3 + be;
   ctx->logr_dec = 3 + bd;
   ctx->logr_mul = prod ? 3 + bm : keep_mul;

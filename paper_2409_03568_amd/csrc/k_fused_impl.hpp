@@ -157,7 +157,7 @@ __global__ void __launch_bounds__(1 << (LOGN - LOGR))
     __attribute__((amdgpu_waves_per_eu(decrypt_waves_per_eu<LOGN, LOGR>())))
     k_hits_fused(FusedJob job, const LimbConsts *__restrict__ lcp, DevTables dt) {
   using S = Shape<LOGN, LOGR>;
-  constexpr int N = S::N, R = S::R, T = S::T;
+  constexpr int N = S::N, R = S::R;
   const LimbConsts &lc = *lcp;
   extern __shared__ __attribute__((aligned(128))) double lds[];
   double *red = lds + S::SLOTS + kCdtSlots;
