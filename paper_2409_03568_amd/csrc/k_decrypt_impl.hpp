@@ -96,12 +96,13 @@ __device__ __forceinline__ void decrypt_limb(double (&x)[32], const uint64_t *c0
       [&](int r) { return u64_to_f64(c0w[r]); });
 }
 
-// sum_j x_j cos(pi j / N) over the workgroup, returned in thread 0, in a fixed order: TC =
-// min(N/8, 1024) chains j = i mod TC, each summed with increasing j, combined by butterflies
-// over 64 consecutive chains and then in sequence.  sums: the exchange space.
-template <int LOGN>
+// sum_j x_j cos(pi j / N) over the workgroup, returned in thread 0, in the order of the prime-field
+// kernel with 2^LOGR values per thread, so that a ciphertext's decoded value does not depend on
+// which kernel a call takes: TC = N / 2^LOGR chains j = i mod TC, each summed with increasing j,
+// combined by butterflies over 64 consecutive chains and then in sequence.  sums: the exchange space.
+template <int LOGN, int LOGR>
 __device__ __forceinline__ double slot0_sum(const double (&x)[32], double *sums, const DevTables &dt) {
-  constexpr int T = Fft<LOGN>::T, TC = (1 << LOGN) / 8 < 1024 ? (1 << LOGN) / 8 : 1024, A = TC / T;  // chains per thread
+  constexpr int T = Fft<LOGN>::T, TC = 1 << (LOGN - LOGR), A = TC / T;  // chains per thread
   const int tid = opaque(threadIdx.x);
   const unsigned p = fft_place<LOGN>((unsigned)tid);
   double acc[A];
@@ -149,8 +150,8 @@ __device__ __forceinline__ DecItem dec_item(const DecJob &job, uint64_t i) {
 // Registers are budgeted for two waves per SIMD; the two-limb form holds limb 0's values across
 // limb 1's transforms (40 registers spilled; with the limbs side by side in one workgroup of
 // twice the threads nothing is spilled, but all of them wait for each other: 8.5 against 6.8 ms
-// per 65,536 at N = 8192).
-template <int LOGN, int RC, int LIMBS>
+// per 65,536 at N = 8192).  LOGR: the order of the decoded sum only.
+template <int LOGN, int LOGR, int RC, int LIMBS>
 __global__ void __launch_bounds__(1 << (LOGN - 5)) __attribute__((amdgpu_waves_per_eu(2)))
     k_decrypt(DecJob job, const LimbConsts *__restrict__ lcp, DevTables dt) {
   constexpr int N = 1 << LOGN;
@@ -183,7 +184,7 @@ __global__ void __launch_bounds__(1 << (LOGN - 5)) __attribute__((amdgpu_waves_p
         computed_here(x[r]);
       }
     }
-    const double s = slot0_sum<LOGN>(x, lds, dt);
+    const double s = slot0_sum<LOGN, LOGR>(x, lds, dt);
     if (threadIdx.x == 0) job.out[it.item] = s * job.inv_scale;
   }
 }

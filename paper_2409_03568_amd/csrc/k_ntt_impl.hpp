@@ -685,16 +685,17 @@ struct FftLaunch {
                        st, c->d_lc, c->dev);
     return hipGetLastError();
   }
-  template <int LIMBS>
+  template <int LOGR, int LIMBS>
   static hipError_t decrypt_as(const ckks_ctx *c, const DecJob &job, uint64_t grid, hipStream_t st) {
-    hipError_t e = set_lds<k_decrypt<LOGN, RC, LIMBS>, B::exchange>();
+    hipError_t e = set_lds<k_decrypt<LOGN, LOGR, RC, LIMBS>, B::exchange>();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_decrypt<LOGN, RC, LIMBS>), dim3((uint32_t)grid), dim3(T), B::exchange, st, job, c->d_lc,
+    hipLaunchKernelGGL((k_decrypt<LOGN, LOGR, RC, LIMBS>), dim3((uint32_t)grid), dim3(T), B::exchange, st, job, c->d_lc,
                        c->dev);
     return hipGetLastError();
   }
+  template <int LOGR>
   static hipError_t decrypt(const ckks_ctx *c, const DecJob &job, int limbs, uint64_t grid, hipStream_t st) {
-    return limbs == 2 ? decrypt_as<2>(c, job, grid, st) : decrypt_as<1>(c, job, grid, st);
+    return limbs == 2 ? decrypt_as<LOGR, 2>(c, job, grid, st) : decrypt_as<LOGR, 1>(c, job, grid, st);
   }
 };
 
@@ -702,6 +703,8 @@ struct FftLaunch {
 template <int LOGN, int LOGR, int RC>
 struct Launch {
   using S = Shape<LOGN, LOGR>;
+  using OnFft = FftLaunch<LOGN, RC>;
+  static constexpr int kLogr = LOGR;
   static hipError_t keygen(const ckks_ctx *c, uint64_t s0, uint64_t s1, hipStream_t st) {
     hipError_t e = set_lds<k_keygen<LOGN, LOGR, RC>, S::lds_bytes>();
     if (e != hipSuccess) return e;
@@ -841,6 +844,16 @@ struct RingLaunch {
     if (job.list_count) return hipErrorInvalidValue;
     return bright ? encrypt_as<kEncPixels, true>(c, job, grid, st) : encrypt_as<kEncPixels, false>(c, job, grid, st);
   }
+  // Which decryption kernel takes a job: see kDecryptFft.
+  static hipError_t decrypt(const ckks_ctx *c, const DecJob &job, int limbs, uint64_t grid, hipStream_t st) {
+    if constexpr (kDecryptFft<LOGN>)
+      if (grid > (uint64_t)c->num_cus)
+        return pick(c, c->logr_dec, [&](auto L) {
+          using K = decltype(L);
+          return K::OnFft::template decrypt<K::kLogr>(c, job, limbs, grid, st);
+        });
+    return pick(c, c->logr_dec, [&](auto L) { return decltype(L)::decrypt(c, job, limbs, grid, st); });
+  }
 };
 
 }  // namespace ckks
@@ -859,10 +872,7 @@ struct RingLaunch {
     return RingLaunch<LOGN>::pick(c, [&](auto L) { return decltype(L)::prepare(c, st); });                          \
   }                                                                                                                 \
   hipError_t launch_decrypt_##LOGN(const ckks_ctx *c, const DecJob &job, int limbs, uint64_t grid, hipStream_t st) { \
-    auto run = [&](auto L) { return decltype(L)::decrypt(c, job, limbs, grid, st); };                               \
-    if constexpr (kDecryptFft<LOGN>)                                                                                \
-      if (grid > (uint64_t)c->num_cus) return RingLaunch<LOGN>::pick(c, run);                                       \
-    return RingLaunch<LOGN>::pick(c, c->logr_dec, run);                                                             \
+    return RingLaunch<LOGN>::decrypt(c, job, limbs, grid, st);                                                      \
   }                                                                                                                 \
   }
 
