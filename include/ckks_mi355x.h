@@ -396,16 +396,19 @@ int ckks_tune_load(ckks_ctx *ctx, const char *path, int *found);
  * chunk_cts ciphertexts owned by the plan, so device memory stays bounded whatever the
  * batch size.  The cache metadata of the whole batch comes first, so hits are grouped by
  * pool member and cache slot over all images (each pair's entries are read from L2 for
- * all its pixels); then one persistent launch assembles every cache hit -- entry + pool
- * member, with the brightness fused in --, writes it to the ring (a workgroup reuses its
- * slots in turn) and decrypts it from the registers that hold its limb-0 rows.  Misses
- * (every pixel without a cache) are encrypted with the brightness and decrypted through the
- * ring, chunk_cts at a time.  (Where limb 0 alone does not decode
+ * all its pixels); then one persistent launch assembles every ciphertext -- entry + pool
+ * member for a cached value, full encryption for a miss or for every pixel without a
+ * cache -- with the brightness fused in, writes it to the ring (a workgroup reuses its
+ * slots in turn) and decrypts it from the registers that hold its limb-0 rows.  With a
+ * VALUE_FULL cache the launch has no encryption path and needs only the decryption's LDS
+ * and registers, so several workgroups share a CU.  Where that is faster -- always at
+ * N = 16384, with large rings or without a cache below -- misses are instead encrypted and
+ * decrypted by kernels of their own, a pair of launches per chunk_cts pixels but at most
+ * 1,024 pairs.  (Where limb 0 alone does not decode
  * exactly, chunks of chunk_cts ciphertexts are produced and then decrypted from the ring
  * with the two-limb lift.)  Ciphertexts equal ckks_encrypt_cached / ckks_encrypt_pixels
- * followed by ckks_add_const, bit for bit; the decrypted values equal ckks_decrypt_pixels
- * of those ciphertexts bit for bit when decryption uses the default width (the decoded
- * sum's rounding follows the workgroup shape), otherwise to a few units in the last place.  A plan runs one batch at a time.
+ * followed by ckks_add_const, and the decrypted values ckks_decrypt_pixels of those
+ * ciphertexts, bit for bit.  A plan runs one batch at a time.
  * With use_graph, the whole chunk sequence is captured once into a HIP graph and
  * replayed while ckks_batch_run is called again with the same arguments.
  */

@@ -434,7 +434,7 @@ int ckks_context_create(const ckks_params *params, int device, ckks_ctx **out) {
     if (e == hipSuccess) e = dev_alloc(t, M);
   if (e == hipSuccess) e = dev_alloc(&d.pk_fft, (size_t)2 * L * 2 * M);
   if (e == hipSuccess) e = dev_alloc(&d.s_hat, (size_t)L * N);
-  if (e == hipSuccess && r.log_n <= 12) e = dev_alloc(&d.pk_hat, (size_t)2 * L * N);
+  if (e == hipSuccess) e = dev_alloc(&d.pk_hat, (size_t)2 * L * N);
   if (e != hipSuccess) {
     free_tables(c);
     delete c;

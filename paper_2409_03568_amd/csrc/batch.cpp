@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "internal.hpp"
+#include "routes.hpp"
 #include "tune_file.hpp"
 
 using namespace ckks;
@@ -93,32 +94,46 @@ void free_plan(ckks_batch_plan *p) {
 // Enqueues one run on stream st (which may be capturing).
 //
 // Ciphertexts are written in full to the ring (of chunk_cts ciphertexts) or to cts_out, with the
-// brightness fused in, and decrypted from there.
+// brightness fused in.
 //
 // When limb 0 decodes exactly (the usual case), the metadata of every pixel is computed first, so
 // that the hit list is ordered by pool member and cache slot over the whole batch and each (entry,
 // pool member) pair is read from L2 for all its pixels at once; one persistent launch then
-// assembles all hits and decrypts them from the registers holding their limb-0 rows.  The misses
-// (every pixel without a cache) are encrypted and decrypted chunk by chunk through the ring; how
-// many chunks of the miss list there are is known only on the device, so the launches cover the
-// case that all pixels miss and those past the count end at once.  Otherwise the batch goes chunk by
-// chunk through the ring, each chunk decrypted from it with the two-limb lift.
+// assembles all ciphertexts and decrypts them from the registers holding their limb-0 rows.  Where
+// batch_route says so, it takes the hits alone, and the misses (every pixel without a cache) are
+// encrypted and decrypted through the ring, a pair of launches for each ring of them; how
+// many there are is known only on the device, so the launches cover the case that all pixels miss
+// and those past the count end at once.  Otherwise the batch goes chunk by chunk through the ring,
+// each chunk decrypted from it with the two-limb lift.
 hipError_t enqueue_run(ckks_batch_plan *p, const RunKey &k, uint32_t n_seg, hipStream_t st) {
   const ckks_ctx *c = p->ctx;
   const uint64_t S = 2 * (uint64_t)c->prm.L * (uint64_t)c->N;
   const bool misses = !p->cache || p->cache->kind != CKKS_CACHE_VALUE_FULL;
   const bool whole = k.dec_limbs == 1;
   const uint64_t ring = whole && k.cts ? k.n : p->cfg.chunk_cts;  // ciphertexts held at a time
-  const uint64_t chunk = whole && p->cache ? k.n : ring;
+  const uint64_t cus = (uint64_t)c->num_cus;
+  const BatchRoute route = misses ? batch_route(c->prm.log_n, p->cache != nullptr, k.n, ring, cus) : kFused;
+  MissGate few, many;  // which of the launches run, where the number of misses decides
+  if (route == kCounted) {
+    few.turn = kFewMisses;
+    many.turn = kManyMisses;
+    few.few_below = many.few_below = (uint32_t)(cus / 2);
+  }
+  const uint64_t chunk = whole && (p->cache || route == kFused) ? k.n : ring;
   for (uint64_t first = 0; first < k.n; first += chunk) {
     const uint64_t cnt = k.n - first < chunk ? k.n - first : chunk;
     uint64_t *out = k.cts ? k.cts + first * S : p->ring;
     hipError_t e = hipSuccess;
-    if (p->cache) {
+    if (p->cache)
       e = launch_value_meta(c, p->cache, k.px + first, cnt, k.first_index + first, k.seed[0], k.seed[1], p->meta,
                             p->miss, p->counters, p->hits, st);
+    if (p->cache || route == kFused) {
       FusedJob job;
+      job.px = k.px + first;
       job.n = cnt;
+      job.first_index = k.first_index + first;
+      job.seed0 = k.seed[0];
+      job.seed1 = k.seed[1];
       job.out = out;
       job.seg_end = p->seg_end;
       job.seg_b = p->seg_b;
@@ -126,19 +141,25 @@ hipError_t enqueue_run(ckks_batch_plan *p, const RunKey &k, uint32_t n_seg, hipS
       job.seg_base = first;
       job.bright_scale = ldexp(c->scale, 1 - c->prm.log_n);
       job.cursor = p->counters + 2;
-      job.counters = p->counters;
-      job.hits = p->hits;
-      job.meta = p->meta;
-      job.entries = p->cache->entries;
-      job.pool = p->cache->pool_cts;
+      if (p->cache) {
+        job.counters = p->counters;
+        job.miss_list = p->miss;
+        job.hits = p->hits;
+        job.meta = p->meta;
+        job.entries = p->cache->entries;
+        job.pool = p->cache->pool_cts;
+      }
       if (whole) {
         job.dec_out = k.out;
         job.inv_scale = 1.0 / c->scale;
         job.ring = k.cts ? 0 : ring;
       }
-      if (e == hipSuccess) e = launch_hits_fused(c, job, st);
+      job.gate = few;
+      if (e == hipSuccess && misses && route != kApart) e = launch_cached_fused(c, job, true, st);
+      job.gate = many;
+      if (e == hipSuccess && (!misses || route != kFused)) e = launch_cached_fused(c, job, false, st);
     }
-    for (uint64_t at = 0; misses && at < cnt && e == hipSuccess; at += ring) {
+    for (uint64_t at = 0; misses && route != kFused && at < cnt && e == hipSuccess; at += ring) {
       const uint64_t m = cnt - at < ring ? cnt - at : ring;
       EncJob job;
       job.px = k.px + first;
@@ -158,6 +179,7 @@ hipError_t enqueue_run(ckks_batch_plan *p, const RunKey &k, uint32_t n_seg, hipS
         job.list_count = dec.list_count = p->counters;
         job.list_first = dec.list_first = at;
         job.compact = dec.compact = whole && !k.cts;
+        job.gate = dec.gate = many;
       }
       e = launch_encrypt(c, job, p->cache ? std::min(m, kListGrid) : m, st);
       if (e != hipSuccess || !whole) continue;

@@ -50,11 +50,29 @@ struct DevTables {
   Cplx *fft_fwd = nullptr, *fft_inv = nullptr;  // [M] factors
   Cplx *pk_fft = nullptr;    // [2][L][2][M] transforms of the low and high pieces of pk, times 1/M
   Cplx *s_fft = nullptr;     // [M] transform of s, times 1/M
-  double *pk_hat = nullptr;  // [2][L][N] NTT domain times N^-1, centered (N <= 4096)
+  double *pk_hat = nullptr;  // [2][L][N] NTT domain times N^-1, centered
   double *s_hat = nullptr;   // [L][N] NTT domain times N^-1, centered
   uint64_t *evk = nullptr;   // [L][L+1][2][N] key-switching keys of s^2, coefficient domain
   double *evk_hat = nullptr; // [L][L+1][2][N] the same in the NTT domain times N^-1, centered
 };
+
+// How many of a list's pixels a cache misses is known only on the device.  Where that decides
+// between kernels, both are launched, and each reads the counters [miss count, hit count] and ends
+// at once unless it is its turn: the misses are few when below `few_below` plus one in `few_share`
+// (0: none) of the hits.
+enum Turn : int { kAnyMisses = 0, kFewMisses = 1, kManyMisses = 2 };
+struct MissGate {
+  int turn = kAnyMisses;
+  uint32_t few_below = 0, few_share = 0;
+};
+#if defined(__HIPCC__)
+__device__ __forceinline__ bool gate_open(const MissGate &g, const uint32_t *counters) {
+  if (g.turn == kAnyMisses) return true;
+  const bool few = counters[0] < (uint64_t)g.few_below + (g.few_share ? counters[1] / g.few_share : 0u);
+  return few == (g.turn == kFewMisses);
+}
+#endif
+
 
 // What to encrypt, in one of three forms (the launcher picks the kernel variant):
 //   pixels:  items 0..n-1 with value px[i] and Philox index first_index + i;
@@ -69,6 +87,7 @@ struct EncJob {
   const uint32_t *list_count = nullptr;
   uint64_t list_first = 0;      // list: from this position of the list, at most n items
   bool compact = false;         // list: the i-th of them goes to out[i], not to out[item]
+  MissGate gate;                // list: on list_count
   uint64_t n = 0;
   uint64_t first_index = 0;
   uint64_t seed0 = 0, seed1 = 0;
@@ -96,15 +115,22 @@ struct DecJob {
   const uint32_t *list_count = nullptr;
   uint64_t list_first = 0;
   bool compact = false;
+  MissGate gate;
 };
 
-// Cache hits in one persistent launch (k_hits_fused): pixels hits[0..counters[1]) (at most n) are
-// entry + pool member as meta[pixel] says, plus the brightness of their image (seg_* as in
-// EncJob), optionally with the decryption of limb 0 into dec_out.
+// A batch in one persistent launch (k_cached_fused): hits hits[0..counters[1]) are entry + pool
+// member as meta[pixel] says; misses miss_list[0..counters[0]), where they are part of the launch,
+// are encrypted in full, as is every pixel 0..n-1 without a cache (counters == NULL).  Both get the
+// brightness of their image (seg_* as in EncJob), optionally the decryption of limb 0 into dec_out.
 struct FusedJob {
+  const uint8_t *px = nullptr;           // with misses
   uint64_t n = 0;
+  uint64_t first_index = 0;
+  uint64_t seed0 = 0, seed1 = 0;
   uint64_t *out = nullptr;               // [n][2][L][N]
-  const uint32_t *counters = nullptr;    // [miss count, hit count]
+  const uint32_t *counters = nullptr;    // [miss count, hit count], or NULL: every pixel a miss
+  MissGate gate;                         // on counters
+  const uint32_t *miss_list = nullptr;
   const uint32_t *hits = nullptr;
   const uint32_t *meta = nullptr;
   const uint64_t *entries = nullptr;
@@ -114,7 +140,7 @@ struct FusedJob {
   uint32_t n_seg = 0;
   uint64_t seg_base = 0;
   double bright_scale = 0.0;
-  uint32_t *cursor = nullptr;            // [kXcds] work cursors, zeroed by the launcher
+  uint32_t *cursor = nullptr;            // [kXcds] work cursors, zero (without counters: zeroed by the launcher)
   double *dec_out = nullptr;             // [n] decrypted slot 0 (limb 0), or NULL
   double inv_scale = 0.0;
   // ring = 0: the ciphertext of pixel t goes to out + t S.  Otherwise out holds `ring`
@@ -299,7 +325,9 @@ hipError_t run_tiles(const ckks_ctx *ctx, const ckks_cache *cache, const uint8_t
                      const uint64_t *K, double out_scale, int dec_limbs, double *d_out, void *mem, hipStream_t st);
 
 // Launchers (return a hipError_t; enqueue on `stream`).
-hipError_t launch_hits_fused(const ckks_ctx *c, const FusedJob &job, hipStream_t stream);
+// misses = false: hits only; the kernel is then compiled without the encryption path
+// (decryption-sized LDS and registers).
+hipError_t launch_cached_fused(const ckks_ctx *c, const FusedJob &job, bool misses, hipStream_t stream);
 hipError_t launch_keygen(const ckks_ctx *c, uint64_t seed0, uint64_t seed1, hipStream_t stream);
 hipError_t launch_keys_prepare(const ckks_ctx *c, hipStream_t stream);
 hipError_t launch_encrypt(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t stream);

@@ -137,6 +137,7 @@ struct DecItem {
 };
 __device__ __forceinline__ uint64_t dec_count(const DecJob &job) {
   if (!job.list) return job.n;
+  if (!gate_open(job.gate, job.list_count)) return 0;
   const uint64_t m = *job.list_count;
   const uint64_t left = m > job.list_first ? m - job.list_first : 0;
   return left < job.n ? left : job.n;

@@ -1,12 +1,16 @@
-// Cache hits in one persistent launch (Sec. 3.2 caching with the randomness of Sec. 3.3) with each
-// image's brightness (Sec. 4.4.2) and optionally the decryption of every ciphertext (Sec. 2.2.2)
-// fused in.  Included by the transform implementation header, whose shapes, transforms and
-// decryption helpers it uses.
+// Batches in one persistent launch (Sec. 3.2 caching with the randomness of Sec. 3.3): each pixel's
+// ciphertext with its image's brightness (Sec. 4.4.2), optionally with its decryption (Sec. 2.2.2)
+// fused in.  Included by the transform implementation header, whose shapes, samplers, transforms,
+// encryption body and decryption helpers it uses.
 //
-// Each workgroup takes every G-th hit (G = the resident grid, XCD-contiguous).  The hit list is
+// The items are the pixels a value cache holds (entry + pool member: a stream of HBM writes) and,
+// with MISSES, those that it misses (full encryption: compute-bound).  Item i of the launch is
+// a miss when floor((i+1) M / (M+H)) > floor(i M / (M+H)) for M misses and H hits, so the
+// two kinds are spread evenly over the item sequence; each workgroup takes every G-th
+// item (G = the resident grid, XCD-contiguous), and at any moment some workgroups of a CU encrypt
+// or transform while others stream.  Without a cache every pixel is a miss.  The hit list is
 // ordered by pool member and cache slot (see k_cache.hip), so consecutive hits, which one XCD
-// processes together, read a few entries from its L2; at any moment some workgroups of a CU
-// stream their ciphertext while others run their transforms.
+// processes together, read a few entries from its L2.
 //
 // With decryption, limb 0 of each ciphertext is produced last and its c0, c1 rows stay in
 // registers, in the layout the decryption's transform starts from: the ciphertext is still
@@ -15,9 +19,8 @@
 // than the transform wants fewer operations (31,500 hits at N = 8192 take 4.53 ms, with the
 // complex transforms' 4 waves per workgroup 4.88; N = 4096: 1.70 and 2.01).
 //
-// Pixels that a cache misses are encrypted and decrypted by the kernels for those, in launches of
-// their own: one kernel with both paths exceeds the instruction cache and took 14.7 ms for
-// 31,500 pixels at N = 8192 without a cache, where the two launches take 10.0.
+// MISSES = false serves the caches without misses and the batches whose misses take the kernels of
+// plain encryption and decryption (batch_route in routes.hpp says which).
 #pragma once
 
 namespace ckks {
@@ -118,10 +121,11 @@ __device__ __forceinline__ double decode_regs(const double (&c0)[1 << LOGR], dou
 }
 
 // What one item of the launch is: its position i in the item sequence (total: no item
-// left), the pixel index, its meta word, and the brightness multiplier of its image.
+// left), the pixel index, the meta word of a hit or the pixel value of a miss, and the
+// brightness multiplier of its image.
 struct ItemDesc {
   uint64_t i, item;
-  uint32_t word;
+  uint32_t word, miss;
   double fb;
 };
 
@@ -138,11 +142,20 @@ __device__ __forceinline__ uint64_t claim_one(uint32_t *cursor, uint64_t total, 
   return total;
 }
 
-__device__ __forceinline__ ItemDesc resolve_item(const FusedJob &job, uint64_t i, uint64_t total) {
-  ItemDesc d{i, 0, 0, 0.0};
+// Item i of M misses and total - M hits: a miss when floor((i+1) M / total) > floor(i M / total).
+template <bool MISSES>
+__device__ __forceinline__ ItemDesc resolve_item(const FusedJob &job, uint64_t i, uint64_t M, uint64_t total) {
+  ItemDesc d{i, 0, 0, 0, 0.0};
   if (i >= total) return d;
-  d.item = job.hits[i];
-  d.word = job.meta[d.item];
+  const uint64_t mb = MISSES ? i * M / total : 0, mb1 = MISSES ? (i + 1) * M / total : 0;  // i, M < 2^32
+  if (MISSES && mb1 > mb) {
+    d.miss = 1;
+    d.item = job.miss_list ? (uint64_t)job.miss_list[mb] : mb;
+    d.word = job.px[d.item];
+  } else {
+    d.item = job.hits[i - mb];
+    d.word = job.meta[d.item];
+  }
   d.fb = job.seg_b[segment_of(job.seg_end, job.n_seg, job.seg_base + d.item)] * job.bright_scale;
   return d;
 }
@@ -152,19 +165,31 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t x) {
   return (uint64_t)hi << 32 | lo;
 }
 
-template <int LOGN, int LOGR, int RC, bool DECRYPT>
+// Without misses the kernel needs only the decryption's LDS and registers, so more workgroups share
+// a CU and one streams its ciphertext while another runs its transforms.
+template <int LOGN, int LOGR, bool MISSES>
+constexpr int fused_waves_hint() {
+  return MISSES ? 1 : decrypt_waves_per_eu<LOGN, LOGR>();
+}
+
+template <int LOGN, int LOGR, int RC, bool DECRYPT, bool MISSES>
 __global__ void __launch_bounds__(1 << (LOGN - LOGR))
-    __attribute__((amdgpu_waves_per_eu(decrypt_waves_per_eu<LOGN, LOGR>())))
-    k_hits_fused(FusedJob job, const LimbConsts *__restrict__ lcp, DevTables dt) {
+    __attribute__((amdgpu_waves_per_eu(fused_waves_hint<LOGN, LOGR, MISSES>())))
+    k_cached_fused(FusedJob job, const LimbConsts *__restrict__ lcp, DevTables dt) {
   using S = Shape<LOGN, LOGR>;
   constexpr int N = S::N, R = S::R;
   const LimbConsts &lc = *lcp;
   extern __shared__ __attribute__((aligned(128))) double lds[];
+  uint64_t *cdt = reinterpret_cast<uint64_t *>(lds + S::SLOTS);
   double *red = lds + S::SLOTS + kCdtSlots;
   const int tid = threadIdx.x;
+  if constexpr (MISSES)
+    for (int i = tid; i < kCdtSlots; i += S::T) cdt[i] = dt.cdt[i];
   const int L = lc.L;
   const uint64_t S_ct = (uint64_t)2 * L * N;
-  const uint64_t total = job.counters[1];  // hits
+  const uint64_t M = !MISSES ? 0 : job.counters ? job.counters[0] : job.n;  // misses (all pixels without a cache)
+  const uint64_t total = M + (job.counters ? job.counters[1] : 0);          // and hits
+  if (total == 0 || (job.counters && !gate_open(job.gate, job.counters))) return;
   // ring: workgroup b owns slots [b K, (b+1) K), K = ring / grid, and cycles through them
   const uint64_t K = job.ring / gridDim.x;
   // Thread 0 claims and resolves the next item (dependent loads: hit list, meta word, image
@@ -174,7 +199,7 @@ __global__ void __launch_bounds__(1 << (LOGN - LOGR))
   __shared__ uint32_t s_region;  // claim state of thread 0 (kept in LDS: no register across the item)
   if (tid == 0) {
     uint32_t region = 0;
-    s_desc[0] = resolve_item(job, claim_one(job.cursor, total, region), total);
+    s_desc[0] = resolve_item<MISSES>(job, claim_one(job.cursor, total, region), M, total);
     s_region = region;
   }
   __syncthreads();
@@ -183,24 +208,44 @@ __global__ void __launch_bounds__(1 << (LOGN - LOGR))
     if (uniform_u64(cd.i) >= total) break;
     const uint64_t item = uniform_u64(cd.item);
     const uint32_t word = __builtin_amdgcn_readfirstlane(cd.word);
+    const bool miss = MISSES && __builtin_amdgcn_readfirstlane(cd.miss) != 0;
     const double fb = __builtin_bit_cast(double, uniform_u64(__builtin_bit_cast(uint64_t, cd.fb)));
     if (tid == 0) {
       uint32_t region = s_region;
-      s_desc[(done + 1) & 1] = resolve_item(job, claim_one(job.cursor, total, region), total);
+      s_desc[(done + 1) & 1] = resolve_item<MISSES>(job, claim_one(job.cursor, total, region), M, total);
       s_region = region;
     }
     const uint64_t ring_slot = job.ring ? blockIdx.x * K + done % K : 0;
     uint64_t *po = job.out + (job.ring ? ring_slot : item) * S_ct;
     double k0[R], k1[R];
-    const uint64_t *pe = job.entries + (uint64_t)((word & 0xffffu) - 1) * S_ct;
-    const uint64_t *pz = job.pool + (uint64_t)(word >> 16) * S_ct;
-    double u[R];
-    for (int l = 1; l < L; l++) {
-      gather_row<LOGN, LOGR, false>(0, l, L, pe, pz, po, fb, lc, dt, u);
-      gather_row<LOGN, LOGR, false>(1, l, L, pe, pz, po, fb, lc, dt, u);
+    if (miss) {
+      if constexpr (MISSES) {  // compiled only where misses can occur
+        uint16_t *smpl = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(lds) + S::enc_smp_at);
+        const int B = lc.B;
+        const double fv = (double)word * lc.enc_scale;
+        uint32_t smp[R] = {};
+        if constexpr (S::kSmpLds)
+          draw_samples<LOGN, false>(smpl, cdt, B, opaque(tid), S::T, job.seed0, job.seed1, job.first_index + item, kTagV,
+                                    kTagE0, kTagE1, true, true, nullptr);
+        else
+          draw_samples<LOGN, LOGR>(smp, reinterpret_cast<uint16_t *>(lds), cdt, B, opaque(tid), job.seed0, job.seed1,
+                                   job.first_index + item, kTagV, kTagE0, kTagE1);
+        double u0[R], u1[R];
+        for (int l = 1; l < L; l++)
+          encrypt_limb_ntt<LOGN, LOGR, RC, true, false>(l, lds, smpl, smp, L, B, fv, fb, po, lc, dt, u0, u1);
+        encrypt_limb_ntt<LOGN, LOGR, RC, true, DECRYPT>(0, lds, smpl, smp, L, B, fv, fb, po, lc, dt, k0, k1);
+      }
+    } else {
+      const uint64_t *pe = job.entries + (uint64_t)((word & 0xffffu) - 1) * S_ct;
+      const uint64_t *pz = job.pool + (uint64_t)(word >> 16) * S_ct;
+      double u[R];
+      for (int l = 1; l < L; l++) {
+        gather_row<LOGN, LOGR, false>(0, l, L, pe, pz, po, fb, lc, dt, u);
+        gather_row<LOGN, LOGR, false>(1, l, L, pe, pz, po, fb, lc, dt, u);
+      }
+      gather_row<LOGN, LOGR, DECRYPT>(1, 0, L, pe, pz, po, fb, lc, dt, k1);
+      gather_row<LOGN, LOGR, DECRYPT>(0, 0, L, pe, pz, po, fb, lc, dt, k0);
     }
-    gather_row<LOGN, LOGR, DECRYPT>(1, 0, L, pe, pz, po, fb, lc, dt, k1);
-    gather_row<LOGN, LOGR, DECRYPT>(0, 0, L, pe, pz, po, fb, lc, dt, k0);
     if constexpr (DECRYPT) {
       const double s = decode_regs<LOGN, LOGR, RC>(k0, k1, lds, red, lc, dt);
       if (tid == 0) job.dec_out[item] = s * job.inv_scale;

@@ -5,7 +5,7 @@ namespace ckks {
 
 #define CKKS_DECLARE_RING(LOGN)                                                                              \
   hipError_t launch_encrypt_##LOGN(const ckks_ctx *, const EncJob &, uint64_t, hipStream_t);                 \
-  hipError_t launch_hits_fused_##LOGN(const ckks_ctx *, const FusedJob &, hipStream_t);                      \
+  hipError_t launch_cached_fused_##LOGN(const ckks_ctx *, const FusedJob &, bool, hipStream_t);               \
   hipError_t launch_keygen_##LOGN(const ckks_ctx *, uint64_t, uint64_t, hipStream_t);                        \
   hipError_t launch_keys_prepare_##LOGN(const ckks_ctx *, hipStream_t);                                      \
   hipError_t launch_decrypt_##LOGN(const ckks_ctx *, const DecJob &, int, uint64_t, hipStream_t);            \
@@ -30,8 +30,8 @@ CKKS_DECLARE_RING(14)
 hipError_t launch_encrypt(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t stream) {
   CKKS_RING_SWITCH(launch_encrypt, job, grid, stream)
 }
-hipError_t launch_hits_fused(const ckks_ctx *c, const FusedJob &job, hipStream_t stream) {
-  CKKS_RING_SWITCH(launch_hits_fused, job, stream)
+hipError_t launch_cached_fused(const ckks_ctx *c, const FusedJob &job, bool misses, hipStream_t stream) {
+  CKKS_RING_SWITCH(launch_cached_fused, job, misses, stream)
 }
 hipError_t launch_keygen(const ckks_ctx *c, uint64_t seed0, uint64_t seed1, hipStream_t stream) {
   CKKS_RING_SWITCH(launch_keygen, seed0, seed1, stream)

@@ -15,6 +15,7 @@
 #include "internal.hpp"
 #include "ntt.hpp"
 #include "philox.hpp"
+#include "routes.hpp"
 
 namespace ckks {
 
@@ -25,11 +26,15 @@ struct Shape : NttShape<LOGN, LOGR> {
   // table, and a reduction area
   static constexpr int SLOTS = LdsSlots<LOGN, LOGR>::value;
   static constexpr size_t lds_bytes = sizeof(double) * ((size_t)SLOTS + kCdtSlots + 64);
-  // encryption: then a second exchange space (the two inverse transforms of a limb run as one
-  // paired transform), the packed samples of the current ciphertext and the guide
-  static constexpr size_t enc_smp_at = lds_bytes + sizeof(double) * (size_t)SLOTS;
-  static constexpr size_t enc_guide_at = enc_smp_at + sizeof(uint16_t) * ((size_t)1 << LOGN);
-  static constexpr size_t enc_lds_bytes = enc_guide_at + (1 << kGuideBits);
+  // encryption: then a second exchange space where it fits (N <= 8192; the two inverse transforms
+  // of a limb then run as one paired transform), and the packed samples of the current ciphertext
+  // where they fit too (else in registers); k_encrypt_ntt adds the samplers' guide
+  static constexpr size_t smp_bytes = sizeof(uint16_t) << LOGN;
+  static constexpr bool kDual = lds_bytes + sizeof(double) * (size_t)SLOTS <= 160 * 1024;
+  static constexpr size_t enc_smp_at = lds_bytes + (kDual ? sizeof(double) * (size_t)SLOTS : 0);
+  static constexpr bool kSmpLds = enc_smp_at + smp_bytes <= 160 * 1024;
+  static constexpr size_t enc_lds_bytes = enc_smp_at + (kSmpLds ? smp_bytes : 0);
+  static constexpr size_t enc_guided_lds_bytes = enc_lds_bytes + (1 << kGuideBits);
 };
 
 // Draw the packed samples of one polynomial triple into LDS: word j of dst holds
@@ -119,6 +124,7 @@ template <int MODE>
 __device__ __forceinline__ uint64_t enc_count(const EncJob &job) {
   if (MODE == kEncEntries && job.list_count) return *job.list_count;
   if (MODE != kEncList) return job.n;
+  if (!gate_open(job.gate, job.list_count)) return 0;
   const uint64_t m = *job.list_count, left = m > job.list_first ? m - job.list_first : 0;
   return left < job.n ? left : job.n;
 }
@@ -414,16 +420,25 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
 template <int LOGN>
 constexpr bool kEncryptNtt = LOGN <= 12;
 
-// One limb of the encryption of the current item, by the whole workgroup (the samples are drawn).
-template <int LOGN, int LOGR, int RC, bool BRIGHT>
-__device__ __forceinline__ void encrypt_limb_ntt(int l, double *lds, const uint16_t *smpl, int L, int B, double fv,
-                                                 double fb, uint64_t *out, const LimbConsts &lc, const DevTables &dt) {
+// One limb of the encryption of the current item, by the whole workgroup (the samples are drawn: in
+// smpl or, where they do not fit LDS, in smp).  With KEEP the canonical values of c0 and c1 are also
+// returned in k0 and k1 (first-pass layout: register r holds coefficient tid + T r).
+template <int LOGN, int LOGR, int RC, bool BRIGHT, bool KEEP>
+__device__ __forceinline__ void encrypt_limb_ntt(int l, double *lds, const uint16_t *smpl,
+                                                 const uint32_t (&smp)[1 << LOGR], int L, int B, double fv, double fb,
+                                                 uint64_t *out, const LimbConsts &lc, const DevTables &dt,
+                                                 double (&k0)[1 << LOGR], double (&k1)[1 << LOGR]) {
   using S = Shape<LOGN, LOGR>;
   using Red = Schedule<LOGN, RC>;
   constexpr int N = S::N, R = S::R, T = S::T;
   const double q = lc.q[l], qinv = lc.qinv[l];
   const int tid = opaque(threadIdx.x);
-  auto sample = [&](int r) { return (uint32_t)smpl[tid + T * r]; };
+  auto sample = [&](int r) -> uint32_t {
+    if constexpr (S::kSmpLds)
+      return (uint32_t)smpl[tid + T * r];
+    else
+      return smp[r];
+  };
   double x[R];
 #pragma unroll
   for (int r = 0; r < R; r++) x[r] = (double)smp_t(sample(r));
@@ -438,26 +453,56 @@ __device__ __forceinline__ void encrypt_limb_ntt(int l, double *lds, const uint1
     y[r] = mulmod(x[r], ld_table(pk0, e), q, qinv);
     y1[r] = mulmod(x[r], ld_table(pk1, e), q, qinv);
   }
-  // c0 and c1 of this limb through one paired inverse transform; the plaintext and
-  // e0 are loaded before its final exchange
-  double add[R];
-  ntt_inverse2<LOGN, LOGR, Red::inv>(y, y1, lds, lds + S::SLOTS + kCdtSlots + 64, tid, dt.tw_inv + (size_t)l * N, q,
-                                     qinv, [&] {
+  // the plaintext (and the brightness) and e0 of coefficient tid + T r
+  auto message = [&](int r) {
+    const double cs = ld_table(dt.cosj, tid + T * r);
+    double m = (double)smp_g(sample(r), kSmpShiftG2, B) + __builtin_rint(fv * cs);
+    if (BRIGHT) m += __builtin_rint(fb * cs);
+    return m;
+  };
+  if constexpr (S::kDual) {
+    // c0 and c1 of this limb through one paired inverse transform; the plaintext and
+    // e0 are loaded before its final exchange
+    double add[R];
+    ntt_inverse2<LOGN, LOGR, Red::inv>(y, y1, lds, lds + S::SLOTS + kCdtSlots + 64, tid, dt.tw_inv + (size_t)l * N, q,
+                                       qinv, [&] {
+#pragma unroll
+      for (int r = 0; r < R; r++) add[r] = message(r);
+    });
+    uint64_t *dst0 = out + (size_t)l * N, *dst1 = out + ((size_t)L + l) * N;
 #pragma unroll
     for (int r = 0; r < R; r++) {
-      const double cs = ld_table(dt.cosj, tid + T * r);
-      add[r] = (double)smp_g(sample(r), kSmpShiftG2, B) + __builtin_rint(fv * cs);
-      if (BRIGHT) add[r] += __builtin_rint(fb * cs);
+      const unsigned c = tid + T * r;
+      const double v0 = canon(y[r] + add[r], q, qinv);
+      const double v1 = canon(y1[r] + (double)smp_g(sample(r), kSmpShiftG3, B), q, qinv);
+      __builtin_nontemporal_store(f64_to_u64(v0), word_at(dst0, c));
+      __builtin_nontemporal_store(f64_to_u64(v1), word_at(dst1, c));
+      if constexpr (KEEP) {
+        k0[r] = v0;
+        k1[r] = v1;
+      }
     }
-  });
-  uint64_t *dst0 = out + (size_t)l * N, *dst1 = out + ((size_t)L + l) * N;
+  } else {
+#pragma unroll 1
+    for (int poly = 0; poly < 2; poly++) {
+      if (poly == 1) {
 #pragma unroll
-  for (int r = 0; r < R; r++) {
-    const unsigned c = tid + T * r;
-    const double v0 = canon(y[r] + add[r], q, qinv);
-    const double v1 = canon(y1[r] + (double)smp_g(sample(r), kSmpShiftG3, B), q, qinv);
-    __builtin_nontemporal_store(f64_to_u64(v0), word_at(dst0, c));
-    __builtin_nontemporal_store(f64_to_u64(v1), word_at(dst1, c));
+        for (int r = 0; r < R; r++) y[r] = y1[r];
+      }
+      double add[R];  // loaded before the final exchange
+      ntt_inverse<LOGN, LOGR, Red::inv>(y, lds, tid, dt.tw_inv + (size_t)l * N, q, qinv, [&] {
+#pragma unroll
+        for (int r = 0; r < R; r++)
+          add[r] = poly == 0 ? message(r) : (double)smp_g(sample(r), kSmpShiftG3, B);
+      });
+      uint64_t *dst = out + ((size_t)poly * L + l) * N;
+#pragma unroll
+      for (int r = 0; r < R; r++) {
+        const double v = canon(y[r] + add[r], q, qinv);
+        __builtin_nontemporal_store(f64_to_u64(v), word_at(dst, tid + T * r));
+        if constexpr (KEEP) (poly == 0 ? k0 : k1)[r] = v;
+      }
+    }
   }
 }
 
@@ -470,7 +515,7 @@ __global__ void __launch_bounds__(1 << (LOGN - LOGR))
   extern __shared__ __attribute__((aligned(128))) double lds[];
   uint64_t *cdt = reinterpret_cast<uint64_t *>(lds + S::SLOTS);
   uint16_t *smpl = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(lds) + S::enc_smp_at);
-  uint8_t *guide = reinterpret_cast<uint8_t *>(lds) + S::enc_guide_at;
+  uint8_t *guide = reinterpret_cast<uint8_t *>(lds) + S::enc_lds_bytes;
   const int tid = threadIdx.x;
   for (int i = tid; i < kCdtSlots; i += T) cdt[i] = dt.cdt[i];
   for (int i = tid; i < (1 << kGuideBits) / 8; i += T) reinterpret_cast<uint64_t *>(guide)[i] = dt.cdt[kCdtSlots + i];
@@ -481,9 +526,11 @@ __global__ void __launch_bounds__(1 << (LOGN - LOGR))
     __syncthreads();
     draw_samples<LOGN, true>(smpl, cdt, B, opaque(tid), T, job.seed0, job.seed1, e.t, kTagV, kTagE0, kTagE1, true, true,
                              guide);
+    const uint32_t unused[S::R] = {};
+    double k0[S::R], k1[S::R];
     for (int l = 0; l < L; l++)
-      encrypt_limb_ntt<LOGN, LOGR, RC, BRIGHT>(l, lds, smpl, L, B, e.fv, e.fb, job.out + e.slot * (uint64_t)(2 * L) * N,
-                                               lc, dt);
+      encrypt_limb_ntt<LOGN, LOGR, RC, BRIGHT, false>(l, lds, smpl, unused, L, B, e.fv, e.fb,
+                                                      job.out + e.slot * (uint64_t)(2 * L) * N, lc, dt, k0, k1);
   }
 }
 
@@ -681,7 +728,7 @@ struct FftLaunch {
     using S = Shape<LOGN, 4>;
     e = set_lds<k_keys_prepare_ntt<LOGN, 4, RC>, S::lds_bytes>();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_keys_prepare_ntt<LOGN, 4, RC>), dim3(c->lc.L, c->dev.pk_hat ? 3 : 1), dim3(S::T), S::lds_bytes,
+    hipLaunchKernelGGL((k_keys_prepare_ntt<LOGN, 4, RC>), dim3(c->lc.L, 3), dim3(S::T), S::lds_bytes,
                        st, c->d_lc, c->dev);
     return hipGetLastError();
   }
@@ -713,10 +760,10 @@ struct Launch {
   }
   template <int MODE, bool BRIGHT>
   static hipError_t encrypt_as(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {
-    hipError_t e = set_lds<k_encrypt_ntt<LOGN, LOGR, RC, MODE, BRIGHT>, S::enc_lds_bytes>();
+    hipError_t e = set_lds<k_encrypt_ntt<LOGN, LOGR, RC, MODE, BRIGHT>, S::enc_guided_lds_bytes>();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_encrypt_ntt<LOGN, LOGR, RC, MODE, BRIGHT>), dim3((uint32_t)grid), dim3(S::T), S::enc_lds_bytes,
-                       st, job, c->d_lc, c->dev);
+    hipLaunchKernelGGL((k_encrypt_ntt<LOGN, LOGR, RC, MODE, BRIGHT>), dim3((uint32_t)grid), dim3(S::T),
+                       S::enc_guided_lds_bytes, st, job, c->d_lc, c->dev);
     return hipGetLastError();
   }
   template <int LIMBS>
@@ -730,10 +777,10 @@ struct Launch {
   static hipError_t decrypt(const ckks_ctx *c, const DecJob &job, int limbs, uint64_t grid, hipStream_t st) {
     return limbs == 2 ? decrypt_as<2>(c, job, grid, st) : decrypt_as<1>(c, job, grid, st);
   }
-  template <bool DECRYPT>
+  template <bool DECRYPT, bool MISSES>
   static hipError_t fused_as(const ckks_ctx *c, const FusedJob &job, hipStream_t st) {
-    constexpr auto kernel = k_hits_fused<LOGN, LOGR, RC, DECRYPT>;
-    constexpr size_t lds = DECRYPT ? S::lds_bytes : 0;
+    constexpr auto kernel = k_cached_fused<LOGN, LOGR, RC, DECRYPT, MISSES>;
+    constexpr size_t lds = MISSES ? S::enc_lds_bytes : DECRYPT ? S::lds_bytes : 0;
     hipError_t e = set_lds<kernel, lds>();
     if (e != hipSuccess) return e;
     // a persistent grid: the workgroups that fit on the device at once
@@ -755,16 +802,17 @@ struct Launch {
       if (!jb.dec_out) return hipErrorInvalidValue;
       if (grid > jb.ring) grid = jb.ring;
     }
-    e = launch_fill_u32(jb.cursor, kXcds, 0u, st);
+    if (!jb.counters) e = launch_fill_u32(jb.cursor, kXcds, 0u, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_hits_fused<LOGN, LOGR, RC, DECRYPT>), dim3((uint32_t)grid), dim3(S::T), lds, st, jb, c->d_lc,
-                       c->dev);
+    hipLaunchKernelGGL((k_cached_fused<LOGN, LOGR, RC, DECRYPT, MISSES>), dim3((uint32_t)grid), dim3(S::T), lds, st, jb,
+                       c->d_lc, c->dev);
     return hipGetLastError();
   }
-  static hipError_t fused(const ckks_ctx *c, const FusedJob &job, hipStream_t st) {
+  static hipError_t fused(const ckks_ctx *c, const FusedJob &job, bool misses, hipStream_t st) {
     if (job.n == 0) return hipSuccess;
-    if (!job.counters || !job.cursor || !job.seg_b) return hipErrorInvalidValue;
-    return job.dec_out ? fused_as<true>(c, job, st) : fused_as<false>(c, job, st);
+    if (!job.cursor || !job.seg_b || (misses ? !job.px : !job.counters)) return hipErrorInvalidValue;
+    if (misses) return job.dec_out ? fused_as<true, true>(c, job, st) : fused_as<false, true>(c, job, st);
+    return job.dec_out ? fused_as<true, false>(c, job, st) : fused_as<false, false>(c, job, st);
   }
   static hipError_t relin_keygen(const ckks_ctx *c, uint64_t s0, uint64_t s1, hipStream_t st) {
     hipError_t e = set_lds<k_relin_keygen<LOGN, LOGR, RC>, S::lds_bytes>();
@@ -822,8 +870,7 @@ struct RingLaunch {
   template <int MODE, bool BRIGHT>
   static hipError_t encrypt_as(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {
     const uint64_t cus = (uint64_t)c->num_cus, n = job.n;
-    constexpr uint64_t few_of[4] = {1, 2, 4, 2};  // up to this many pixels per 4 CUs
-    if (n && n <= grid && 4 * n <= few_of[LOGN - 11] * cus)
+    if (n && n <= grid && 4 * n <= few_per_4_cus(LOGN) * cus)
       return pick(c, [&](auto L) { return decltype(L)::template encrypt_few<MODE, BRIGHT>(c, job, st); });
     if constexpr (kEncryptNtt<LOGN>)
       if (n < (LOGN == 11 ? 32 : 2) * cus)
@@ -893,7 +940,7 @@ struct RingLaunch {
 
 #define CKKS_DEFINE_RING_FUSED(LOGN)                                                                                \
   namespace ckks {                                                                                                  \
-  hipError_t launch_hits_fused_##LOGN(const ckks_ctx *c, const FusedJob &job, hipStream_t st) {                     \
-    return RingLaunch<LOGN>::pick(c, c->logr_dec, [&](auto L) { return decltype(L)::fused(c, job, st); });          \
+  hipError_t launch_cached_fused_##LOGN(const ckks_ctx *c, const FusedJob &job, bool misses, hipStream_t st) {       \
+    return RingLaunch<LOGN>::pick(c, c->logr_dec, [&](auto L) { return decltype(L)::fused(c, job, misses, st); });  \
   }                                                                                                                 \
   }
