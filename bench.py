@@ -176,16 +176,16 @@ def encrypt_ops_per_ct(log_n, L):
     return 6 * (1 + 4 * L) * (M // 2) * (log_n - 1) + 2 * L * (4 * 4 * M + 8 * N)
 
 
-def mul_ops_per_pair(log_n, level):
-    """Algorithmic FP64 VALU operations of one relinearized product at `level` limbs:
-    5 transforms per limb for the tensor product (4 forward, 1 inverse for d2), in the
-    special prime level forward and 2 inverse transforms, in each q_j level - 1 forward
+def mul_ops_per_square(log_n, level):
+    """Algorithmic FP64 VALU operations of one relinearized product of a ciphertext with itself at
+    `level` limbs: 3 transforms per limb for the tensor product (2 forward, 1 inverse for d2), in
+    the special prime level forward and 2 inverse transforms, in each q_j level - 1 forward
     (digit j's transform comes from the tensor step) and 2 inverse transforms (8 ops per
-    butterfly); per element 7 pointwise products per limb (tensor), 2 per digit and
+    butterfly); per element 6 pointwise products per limb (tensor), 2 per digit and
     prime (key switching) and 4 per limb (ModDown), 6 ops each."""
     N = 1 << log_n
-    transforms = 5 * level + (level + 2) + level * (level + 1)
-    products = 7 * level + 2 * level * (level + 1) + 4 * level
+    transforms = 3 * level + (level + 2) + level * (level + 1)
+    products = 6 * level + 2 * level * (level + 1) + 4 * level
     return 8 * transforms * (N // 2) * log_n + 6 * products * N
 
 
@@ -243,14 +243,14 @@ def matching_bench(P, W, runs):
     diff = a_img.astype(np.int64).reshape(-1) - b_img.astype(np.int64).reshape(-1)
     l1 = float(np.sqrt(np.rint(got).clip(0)).sum())
     best = tune["mul_width"]
-    ops = mul_ops_per_pair(c.log_n, c.num_primes) * n
+    ops = mul_ops_per_square(c.log_n, c.num_primes) * n
     ach = ops / (ms["mul"] / 1e3) / 1e12
     res = {"pairs": int(n), "ms": {k: round(v, 3) for k, v in ms.items()}, "total_ms": round(total, 3),
            "pairs_per_s": round(n / (total / 1e3)),
            "autotune_8192_pairs_ms": {w: {str(k): round(v, 3) for k, v in tune[w + "_ms"].items()}
                                       for w in ("encrypt", "decrypt", "mul")},
-           "mul_roofline": {"bound": "alu", "kernel": "k_mul<13, %d, 1> (tensor, key switch, ModDown; %d values "
-                                                      "per thread)" % (best.bit_length() - 1, best),
+           "mul_roofline": {"bound": "alu", "kernel": "k_mul<13, %d, 1, true> (square: tensor, key switch, ModDown; "
+                                                      "%d values per thread)" % (best.bit_length() - 1, best),
                             "achieved": round(ach, 3), "peak": round(PEAK_VALU_OPS / 1e12, 3),
                             "unit": "TVALUop/s (FP64)", "frac": round(ach * 1e12 / PEAK_VALU_OPS, 4)},
            "max_sq_err": float(np.max(np.abs(got - diff.astype(np.float64) ** 2))),
