@@ -28,13 +28,16 @@ struct Shape : NttShape<LOGN, LOGR> {
   static constexpr size_t lds_bytes = sizeof(double) * ((size_t)SLOTS + kCdtSlots + 64);
   // encryption: then a second exchange space where it fits (N <= 8192; the two inverse transforms
   // of a limb then run as one paired transform), and the packed samples of the current ciphertext
-  // where they fit too (else in registers); k_encrypt_ntt adds the samplers' guide
+  // where they fit too (else in registers); k_encrypt_ntt adds the samplers' guide, but at N = 2048
+  // goes without: four workgroups share a CU there, with the guide's LDS three, and its loads cost
+  // small calls more than its search saves (100 pixels 41.3 against 40.9 us, 8,000 428 against 411)
   static constexpr size_t smp_bytes = sizeof(uint16_t) << LOGN;
   static constexpr bool kDual = lds_bytes + sizeof(double) * (size_t)SLOTS <= 160 * 1024;
   static constexpr size_t enc_smp_at = lds_bytes + (kDual ? sizeof(double) * (size_t)SLOTS : 0);
   static constexpr bool kSmpLds = enc_smp_at + smp_bytes <= 160 * 1024;
   static constexpr size_t enc_lds_bytes = enc_smp_at + (kSmpLds ? smp_bytes : 0);
-  static constexpr size_t enc_guided_lds_bytes = enc_lds_bytes + (1 << kGuideBits);
+  static constexpr int enc_guide = LOGN == 11 ? 0 : kGuideBits;
+  static constexpr size_t enc_guided_lds_bytes = enc_lds_bytes + (enc_guide ? 1 << enc_guide : 0);
 };
 
 // Draw the packed samples of one polynomial triple into LDS: word j of dst holds
@@ -412,13 +415,13 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
 }
 
 // ---------------------------------------------------------------------------
-// The same through prime-field transforms, for N = 2^11 and 2^12: x = NTT(v) per limb, c0 =
+// The same through prime-field transforms, for N <= 8192: x = NTT(v) per limb, c0 =
 // INTT(x pk0^) + e0 + m, c1 = INTT(x pk1^) + e1.  N/8 threads per ciphertext where the complex
 // transforms have N/32, so it has the lower latency where whole ciphertexts just fill the device
-// (RingLaunch::encrypt).
+// (encrypt_kernel in routes.hpp).
 // ---------------------------------------------------------------------------
 template <int LOGN>
-constexpr bool kEncryptNtt = LOGN <= 12;
+constexpr bool kEncryptNtt = LOGN <= 13;
 
 // One limb of the encryption of the current item, by the whole workgroup (the samples are drawn: in
 // smpl or, where they do not fit LDS, in smp).  With KEEP the canonical values of c0 and c1 are also
@@ -518,13 +521,14 @@ __global__ void __launch_bounds__(1 << (LOGN - LOGR))
   uint8_t *guide = reinterpret_cast<uint8_t *>(lds) + S::enc_lds_bytes;
   const int tid = threadIdx.x;
   for (int i = tid; i < kCdtSlots; i += T) cdt[i] = dt.cdt[i];
-  for (int i = tid; i < (1 << kGuideBits) / 8; i += T) reinterpret_cast<uint64_t *>(guide)[i] = dt.cdt[kCdtSlots + i];
+  if constexpr (S::enc_guide != 0)
+    for (int i = tid; i < (1 << S::enc_guide) / 8; i += T) reinterpret_cast<uint64_t *>(guide)[i] = dt.cdt[kCdtSlots + i];
   const int L = lc.L, B = lc.B;
   const uint64_t count = enc_count<MODE>(job);
   for (uint64_t it = blockIdx.x; it < count; it += gridDim.x) {
     const EncItem e = enc_item<MODE, BRIGHT>(job, it, lc);
     __syncthreads();
-    draw_samples<LOGN, true>(smpl, cdt, B, opaque(tid), T, job.seed0, job.seed1, e.t, kTagV, kTagE0, kTagE1, true, true,
+    draw_samples<LOGN, S::enc_guide != 0>(smpl, cdt, B, opaque(tid), T, job.seed0, job.seed1, e.t, kTagV, kTagE0, kTagE1, true, true,
                              guide);
     const uint32_t unused[S::R] = {};
     double k0[S::R], k1[S::R];
@@ -861,19 +865,14 @@ struct RingLaunch {
     if (logr == 5) return c->rc ? f(Launch<LOGN, 5, 1>{}) : f(Launch<LOGN, 5, 0>{});
     return hipErrorInvalidValue;
   }
-  // Which encryption kernel takes a job (of a list: by its largest length).  In us for n pixels, split / prime-field / whole
-  // ciphertexts by complex transforms:
-  //   N = 2048:   n = 64: 24 / 26 / 66   200: 35 / 27 / 66   3,200: - / 172 / 187   10,000: - / 538 / 504
-  //   N = 4096:   n = 128: 38 / 39 / 71  200: 54 / 41 / 71   400: 75 / 65 / 95      800: - / 118 / 108
-  //   N = 8192:   n = 64: 43 / 92 / 103  128: 66 / 95 / 102  200: 98 / 99 / 103     400: - / 186 / 149
-  //   N = 16384:  n = 64: 110 / 340 / 240  128: 180 / 350 / 265   200: - / 357 / 272
   template <int MODE, bool BRIGHT>
   static hipError_t encrypt_as(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {
-    const uint64_t cus = (uint64_t)c->num_cus, n = job.n;
-    if (n && n <= grid && 4 * n <= few_per_4_cus(LOGN) * cus)
+    if (job.n == 0) return hipSuccess;
+    const EncKernel kernel = encrypt_kernel(LOGN, c->lc.L, job.n, (uint64_t)c->num_cus);
+    if (kernel == kEncSplit && job.n <= grid)
       return pick(c, [&](auto L) { return decltype(L)::template encrypt_few<MODE, BRIGHT>(c, job, st); });
     if constexpr (kEncryptNtt<LOGN>)
-      if (n < (LOGN == 11 ? 32 : 2) * cus)
+      if (kernel == kEncPrime)
         return pick(c, c->logr_enc,
                     [&](auto L) { return decltype(L)::template encrypt_as<MODE, BRIGHT>(c, job, grid, st); });
     return pick(c, [&](auto L) { return decltype(L)::template encrypt_as<MODE, BRIGHT>(c, job, grid, st); });

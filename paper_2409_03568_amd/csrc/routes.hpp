@@ -5,9 +5,52 @@
 
 namespace ckks {
 
-// Encryption splits a pixel's rows over workgroups (k_encrypt_few) up to this many pixels per 4
-// CUs: see RingLaunch::encrypt_as.
-constexpr uint64_t few_per_4_cus(int log_n) { return log_n == 11 ? 1 : log_n == 13 ? 4 : 2; }
+// Which kernel encrypts n pixels (of a list: by its capacity): a pixel's rows split over workgroups
+// (k_encrypt_few), whole ciphertexts through prime-field transforms (k_encrypt_ntt, N <= 8192) or
+// through complex ones (k_encrypt).  The complex transforms take less work from two or three primes
+// on, where their one transform of v serves all, but a workgroup of theirs has a quarter of the
+// threads, so a round of workgroups that leaves CUs part empty wants the prime-field ones.  In us,
+// split / prime-field / complex, for n pixels on 256 CUs:
+//   N = 2048, 1 prime:    64: 33 / 31 / 57   2,048: - / 66 / 74     10,240: - / 234 / 276
+//             3 primes:   64: 39 / 41 / 82   2,560: - / 145 / 173   10,240: - / 516 / 505
+//             4 primes:  128: 54 / 47 / 94   2,048: - / 149 / 144    3,072: - / 209 / 214   8,192: - / 529 / 494
+//             8 primes:   64: 53 / 69 / 144  1,536: - / 207 / 216    2,560: - / 320 / 339   3,072: - / 391 / 352
+//   N = 4096, 1 prime:   128: 38 / 36 / 60   4,096: - / 210 / 253   16,384: - / 778 / 863
+//             2 primes:  128: 47 / 45 / 74   6,144: - / 495 / 493   10,240: - / 814 / 788
+//             3 primes:  128: 55 / 55 / 88     768: - / 108 / 114    1,024: - / 132 / 125   1,536: - / 182 / 214
+//                      2,560: - / 294 / 308  4,096: - / 450 / 438    8,192: - / 904 / 833
+//             8 primes:  512: - / 168 / 215    768: - / 233 / 222    1,500: - / 412 / 430   2,560: - / 690 / 637
+//   N = 8192, 1 prime:   192: 67 / 50 / 66     512: - / 84 / 80        768: - / 114 / 118   1,536: - / 204 / 197
+//             4 primes:  128: 84 / 106 / 118   192: 118 / 108 / 118    256: 119 / 112 / 119   512: - / 202 / 165
+//            16 primes:  192: 315 / 337 / 339  256: 320 / 350 / 342    512: - / 711 / 513
+//   N = 16384, 4 primes: 128: 195 / - / 283    192: 310 / - / 288
+enum EncKernel : int { kEncSplit = 0, kEncPrime = 1, kEncComplex = 2 };
+inline EncKernel encrypt_kernel(int log_n, int primes, uint64_t n, uint64_t cus) {
+  if (log_n == 14) return 2 * n <= cus ? kEncSplit : kEncComplex;
+  if (log_n == 13) {
+    if (2 * n <= cus || (primes > 2 && 3 * n <= 2 * cus) || (primes >= 8 && n <= cus)) return kEncSplit;
+    if (n <= cus) return kEncPrime;
+  } else if (primes > 1 && (log_n == 11 ? 4 : 2) * n <= cus) {
+    return kEncSplit;
+  }
+  // complex from `from` pixels per CU on, and before that where the last round of as many
+  // ciphertexts as the device holds is filled beyond `last` per CU (0: never)
+  constexpr uint64_t kNever = ~0ull;
+  uint64_t from, last;
+  if (log_n == 11) {
+    from = primes < 3 ? kNever : primes < 8 ? 32 : 12;
+    last = primes < 4 ? 0 : 6;
+  } else if (log_n == 12) {
+    from = primes < 2 ? kNever : primes < 3 ? 32 : primes < 8 ? 20 : 8;
+    last = primes < 3 ? 0 : primes < 8 ? 3 : 2;
+  } else {
+    from = primes < 2 ? 5 : 1;
+    last = 1;
+  }
+  const uint64_t round = (uint64_t)(1 << (14 - log_n)) * cus;  // ciphertexts on the device at once
+  if (from != kNever && n >= from * cus) return kEncComplex;
+  return last && (n - 1) % round + 1 > last * cus ? kEncComplex : kEncPrime;
+}
 
 // How the misses of a batch (every pixel without a cache) are encrypted and decrypted: by the
 // batch's persistent launch (k_cached_fused), which does with one workgroup's share of the ring and

@@ -47,8 +47,34 @@ static void batches() {
   CHECK(batch_route(13, false, 30000, 64, 256) == kApart);
 }
 
+static void encryption() {
+  for (uint64_t cus : {64ull, 256ull, 304ull})
+    for (int log_n = 11; log_n <= 14; log_n++)
+      for (int primes = 1; primes <= 16; primes++)
+        for (uint64_t n = 1; n < 100000; n += n < 5000 ? 1 : 997) {
+          const EncKernel k = encrypt_kernel(log_n, primes, n, cus);
+          if (k == kEncSplit) CHECK(n <= cus);       // parts of at least one workgroup per CU
+          if (k == kEncPrime) CHECK(log_n <= 13);    // the kernels that are compiled
+          // a single prime leaves the complex transforms nothing to share at small rings
+          if (log_n <= 12 && primes == 1) CHECK(k == kEncPrime);
+          // at N = 8192 a round that leaves CUs part empty takes the prime-field kernel
+          if (log_n == 13 && primes < 8 && 3 * n > 2 * cus && n <= cus) CHECK(k == kEncPrime);
+          if (log_n == 13 && primes > 1 && n > cus) CHECK(k == kEncComplex);
+        }
+  CHECK(encrypt_kernel(12, 3, 700, 256) == kEncPrime);
+  CHECK(encrypt_kernel(12, 3, 1024, 256) == kEncComplex);
+  CHECK(encrypt_kernel(12, 3, 1500, 256) == kEncPrime);
+  CHECK(encrypt_kernel(12, 3, 65536, 256) == kEncComplex);
+  CHECK(encrypt_kernel(11, 8, 1000, 256) == kEncPrime);
+  CHECK(encrypt_kernel(11, 8, 2048, 256) == kEncComplex);
+  CHECK(encrypt_kernel(13, 2, 200, 256) == kEncPrime);
+  CHECK(encrypt_kernel(13, 4, 129, 256) == kEncSplit);
+  CHECK(encrypt_kernel(13, 12, 256, 256) == kEncSplit);
+}
+
 int main() {
   batches();
+  encryption();
   if (!failures) printf("ok\n");
   return failures != 0;
 }
