@@ -194,13 +194,7 @@ __global__ void __launch_bounds__(1 << (LOGN - 5)) __attribute__((amdgpu_waves_p
 // The same through prime-field transforms (ntt.hpp), with 8 or 16 values per thread and so two to
 // four times the waves.
 // ---------------------------------------------------------------------------
-// The complex transforms decrypt where there is the choice: at N = 8192, from one ciphertext per
-// CU on.  Per 65,536 one-limb and two-limb decryptions they take there 3.41 and 6.80 ms, the
-// prime-field ones 3.56 and 7.84; for 200 ciphertexts 37 and 35 us.  At N = 4096 they win only
-// for many ciphertexts (3.08 against 3.12 ms per 65,536, 173 against 159 us for 3,200); at N =
-// 2048, whose smaller primes need fewer reductions, they lose (1.43 against 1.36 ms), and at
-// 2^14, whose 128 KB exchange space leaves one workgroup of 8 waves on a CU, too (20.7 against
-// 16.9 ms).
+// Which of the two decrypts: decrypt_complex in routes.hpp.
 template <int LOGN>
 constexpr bool kDecryptFft = LOGN == 13;
 

@@ -890,10 +890,9 @@ struct RingLaunch {
     if (job.list_count) return hipErrorInvalidValue;
     return bright ? encrypt_as<kEncPixels, true>(c, job, grid, st) : encrypt_as<kEncPixels, false>(c, job, grid, st);
   }
-  // Which decryption kernel takes a job: see kDecryptFft.
   static hipError_t decrypt(const ckks_ctx *c, const DecJob &job, int limbs, uint64_t grid, hipStream_t st) {
     if constexpr (kDecryptFft<LOGN>)
-      if (grid > (uint64_t)c->num_cus)
+      if (decrypt_complex(LOGN, c->rc, limbs, grid, (uint64_t)c->num_cus))
         return pick(c, c->logr_dec, [&](auto L) {
           using K = decltype(L);
           return K::OnFft::template decrypt<K::kLogr>(c, job, limbs, grid, st);

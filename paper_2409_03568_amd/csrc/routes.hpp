@@ -52,6 +52,23 @@ inline EncKernel encrypt_kernel(int log_n, int primes, uint64_t n, uint64_t cus)
   return last && (n - 1) % round + 1 > last * cus ? kEncComplex : kEncPrime;
 }
 
+// Whether n ciphertexts are decrypted through complex transforms (else through prime-field ones).
+// They win where there are many ciphertexts of N = 8192, and earlier for two limbs and for primes
+// of more than 40 bits (prime_class 1), whose prime-field transforms need more reductions.  In
+// us, prime-field / complex:
+//   50 bits, one limb   300: 43.7 / 45.7   2,000: 122 / 126   3,000: 178 / 178   8,000: 448 / 420
+//            two limbs  200: 35 / 37       300: 77.7 / 74.1   2,000: 264 / 238   8,000: 982 / 832
+//   36 bits, one limb   300: 42.9 / 45.7   2,000: 117 / 125   5,000: 267 / 273   8,000: 417 / 416
+//            two limbs  300: 74.5 / 74.2   511: 77.2 / 78.5   1,000: 136 / 134   8,000: 933 / 831
+// At N = 4096 the complex ones win only for many ciphertexts (3.08 against 3.12 ms per 65,536, 173
+// against 159 us for 3,200); at N = 2048, whose smaller primes need fewer reductions, they lose
+// (1.43 against 1.36 ms), and at 2^14, whose 128 KB exchange space leaves one workgroup of 8 waves
+// on a CU, too (20.7 against 16.9 ms).
+inline bool decrypt_complex(int log_n, int prime_class, int limbs, uint64_t n, uint64_t cus) {
+  const uint64_t per_cu = limbs == 2 ? (prime_class ? 1 : 3) : prime_class ? 16 : 32;
+  return log_n == 13 && n > per_cu * cus;
+}
+
 // How the misses of a batch (every pixel without a cache) are encrypted and decrypted: by the
 // batch's persistent launch (k_cached_fused), which does with one workgroup's share of the ring and
 // no launch of its own, or apart, by the kernels of plain encryption and decryption, a pair of

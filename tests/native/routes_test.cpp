@@ -72,7 +72,18 @@ static void encryption() {
   CHECK(encrypt_kernel(13, 12, 256, 256) == kEncSplit);
 }
 
+static void decryption() {
+  for (int log_n : {11, 12, 14}) CHECK(!decrypt_complex(log_n, 1, 2, 1000000, 256));
+  // few ciphertexts, and one limb up to several rounds of workgroups, take the prime-field kernel
+  for (uint64_t n : {1ull, 256ull}) CHECK(!decrypt_complex(13, 1, 2, n, 256));
+  for (uint64_t n : {300ull, 700ull, 2000ull}) CHECK(!decrypt_complex(13, 1, 1, n, 256) && !decrypt_complex(13, 0, 1, n, 256));
+  CHECK(!decrypt_complex(13, 0, 2, 511, 256));
+  CHECK(decrypt_complex(13, 1, 2, 300, 256) && decrypt_complex(13, 0, 2, 1000, 256));
+  CHECK(decrypt_complex(13, 1, 1, 8000, 256) && decrypt_complex(13, 0, 1, 10000, 256));
+}
+
 int main() {
+  decryption();
   batches();
   encryption();
   if (!failures) printf("ok\n");

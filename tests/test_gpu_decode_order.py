@@ -15,7 +15,7 @@ def test_value_is_independent_of_the_call_size(width, level):
         pytest.skip("no GPU")
     import paper_2409_03568_amd as P
 
-    n = 16 * torch.cuda.get_device_properties(0).multi_processor_count
+    n = 17 * torch.cuda.get_device_properties(0).multi_processor_count
     print("[gpu] decode order, width %d, level %d, %d ciphertexts" % (width, level, n), flush=True)
     ctx = P.Context(13, 4, 50, 40)
     ctx.set_ntt_width(width)
