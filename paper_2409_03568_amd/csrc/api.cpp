@@ -13,6 +13,7 @@
 #include "fft.hpp"
 #include "modarith.hpp"
 #include "philox.hpp"
+#include "routes.hpp"
 
 using namespace ckks;
 
@@ -222,14 +223,20 @@ hipError_t encrypt_cached_ws(const ckks_ctx *ctx, const ckks_cache *cache, const
   // The misses (compute-bound full encryptions) run on the auxiliary stream beside the hit
   // gather (bound by HBM writes).  The gather's grid is bounded so that it leaves the CUs room for
   // encryptions (65,536 pixels at N = 8192, 1 or 2 workgroups per CU: 7.12 and 7.44 ms; at
-  // N = 16384, whose CUs hold one encryption, 10,000 pixels with 1 or 4: 5.3 and 4.6 ms).  The
-  // encryption's is that of a list: with one workgroup per CU the same pixels take 6.86 ms at
-  // N = 8192 when one in twelve misses, but 19.5 instead of 14.0 when three in four do.
+  // N = 16384, whose CUs hold one encryption, 10,000 pixels with 1 or 4: 5.3 and 4.6 ms).
   hipEvent_t fork = nullptr, join = nullptr;
   e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&join, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventRecord(fork, st);
   if (e == hipSuccess) e = hipStreamWaitEvent(ctx->aux, fork, 0);
+  const MissRoute r = miss_route(ctx->prm.log_n, n, (uint64_t)ctx->num_cus);
+  if (r.few_share) {
+    job.gate = MissGate{kFewMisses, 0, r.few_share};
+    job.kernel = r.few;
+    if (e == hipSuccess) e = launch_encrypt(ctx, job, r.few_grid ? r.few_grid : std::min<uint64_t>(n, kListGrid), ctx->aux);
+    job.gate.turn = kManyMisses;
+  }
+  job.kernel = r.many;
   if (e == hipSuccess) e = launch_encrypt(ctx, job, std::min<uint64_t>(n, kListGrid), ctx->aux);
   if (e == hipSuccess) e = hipEventRecord(join, ctx->aux);
   if (e == hipSuccess)

@@ -88,6 +88,7 @@ struct EncJob {
   uint64_t list_first = 0;      // list: from this position of the list, at most n items
   bool compact = false;         // list: the i-th of them goes to out[i], not to out[item]
   MissGate gate;                // list: on list_count
+  int kernel = -1;              // EncKernel (routes.hpp), or -1: by n
   uint64_t n = 0;
   uint64_t first_index = 0;
   uint64_t seed0 = 0, seed1 = 0;

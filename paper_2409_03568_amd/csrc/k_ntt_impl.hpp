@@ -868,7 +868,7 @@ struct RingLaunch {
   template <int MODE, bool BRIGHT>
   static hipError_t encrypt_as(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {
     if (job.n == 0) return hipSuccess;
-    const EncKernel kernel = encrypt_kernel(LOGN, c->lc.L, job.n, (uint64_t)c->num_cus);
+    const int kernel = job.kernel >= 0 ? job.kernel : encrypt_kernel(LOGN, c->lc.L, job.n, (uint64_t)c->num_cus);
     if (kernel == kEncSplit && job.n <= grid)
       return pick(c, [&](auto L) { return decltype(L)::template encrypt_few<MODE, BRIGHT>(c, job, st); });
     if constexpr (kEncryptNtt<LOGN>)

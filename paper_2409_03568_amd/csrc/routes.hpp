@@ -69,6 +69,36 @@ inline bool decrypt_complex(int log_n, int prime_class, int limbs, uint64_t n, u
   return log_n == 13 && n > per_cu * cus;
 }
 
+// How the misses of a value cache among n pixels are encrypted, beside the gather of the hits on
+// another stream.  Complex encryptions fill a CU's registers, so where they come first they hold up
+// the gather: few misses take fewer workgroups or the prime-field kernel, many the whole device.  Which it
+// is the device decides, by the misses being below one in `few_share` of the hits (0: not asked,
+// `many` takes any).  few_grid: workgroups (0: as for many).  In us, misses being 1 in 6 / 1 in 3 or
+// 2 in 5 / 3 in 4 of the pixels:
+//   N = 2048, 10,000 pixels: prime-field, 1 per CU 302 / 441 / 741, 2 per CU 312 / 323 / 523,
+//                            unbounded 369 / 347 / 445; complex 418 / 433 / 481
+//             65,536 pixels: prime-field, 1 per CU 1422 / 2580 / 4478, 2 per CU 1318 / 1944 / 3164,
+//                            unbounded 1558 / 1780 / 2767; complex 1351 / 1827 / 2672
+//   N = 4096, 10,000 pixels: prime-field, 1 per CU 510 / 677 / 1072, unbounded 481 / 586 / 895;
+//                            complex 764 / 811 / 865
+//   N = 8192, 10,000 pixels: prime-field, 1 per CU 1312 / 1739 / 2971; complex, 1 per CU
+//                            1132 / 1679 / 2934, unbounded 1582 / 1625 / 2380
+//             65,536 pixels: complex, 1 per CU 7025 / 11883 / 19574, unbounded 6761 / 10037 / 14817
+//   1,024 pixels, prime-field unbounded against complex: N = 2048 109 / 112 / 123 against 144 / 142 / 148,
+//   N = 4096 134 / 137 / 169 against 148 / 163 / 191, N = 8192 217 / 270 / 357 against 206 / 224 / 310
+struct MissRoute {
+  uint32_t few_share;
+  int few, many;      // EncKernel, -1: by n
+  uint64_t few_grid;
+};
+inline MissRoute miss_route(int log_n, uint64_t n, uint64_t cus) {
+  if (log_n == 14 || n <= (log_n == 13 ? 4 : 1) * cus) return MissRoute{0, -1, -1, 0};
+  if (log_n == 13) return MissRoute{2, kEncComplex, kEncComplex, cus};
+  if (n <= 4 * cus) return MissRoute{0, kEncPrime, kEncPrime, 0};
+  if (log_n == 12) return MissRoute{1, kEncPrime, kEncComplex, 0};
+  return MissRoute{2, kEncPrime, kEncPrime, (n < 128 * cus ? 1 : 2) * cus};
+}
+
 // How the misses of a batch (every pixel without a cache) are encrypted and decrypted: by the
 // batch's persistent launch (k_cached_fused), which does with one workgroup's share of the ring and
 // no launch of its own, or apart, by the kernels of plain encryption and decryption, a pair of

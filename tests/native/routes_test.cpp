@@ -82,8 +82,22 @@ static void decryption() {
   CHECK(decrypt_complex(13, 1, 1, 8000, 256) && decrypt_complex(13, 0, 1, 10000, 256));
 }
 
+static void cached_misses() {
+  for (int log_n = 11; log_n <= 14; log_n++)
+    for (uint64_t n : {1ull, 256ull, 1024ull, 1025ull, 4000ull, 65536ull}) {
+      const MissRoute r = miss_route(log_n, n, 256);
+      // complex encryptions of the whole device beside the gather only for many misses
+      if (r.few_share) CHECK(r.few != kEncComplex || r.few_grid == 256);
+      if (r.few_share) CHECK(n > 1024 && log_n < 14);
+      if (log_n == 14) CHECK(r.many < 0);  // kernels that are compiled
+      if (log_n == 11 && n > 256) CHECK(r.many == kEncPrime);
+      if (log_n == 12 && n > 1024) CHECK(r.few == kEncPrime && r.many == kEncComplex);
+    }
+}
+
 int main() {
   decryption();
+  cached_misses();
   batches();
   encryption();
   if (!failures) printf("ok\n");

@@ -1,0 +1,43 @@
+"""Value-cached encryption through each choice that the device makes by the number of misses: few
+misses, about half, and nearly all, on both sides of the lines, against plain encryption of the
+missed pixels and the gather of the others by a small call."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+RINGS = {11: (3, 30, 20), 12: (3, 36, 30), 13: (2, 50, 40), 14: (1, 50, 38)}
+
+
+@pytest.mark.parametrize("log_n", [11, 12, 13, 14])
+@pytest.mark.parametrize("n", [200, 1100, 1500])
+@pytest.mark.parametrize("missing", [0.0, 0.02, 0.3, 0.34, 0.5, 0.95, 1.0])
+def test_every_share_of_misses(log_n, n, missing):
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2409_03568_amd as P
+
+    print("[gpu] misses N=2^%d, %d pixels, %.2f missing" % (log_n, n, missing), flush=True)
+    ctx = P.Context(log_n, *RINGS[log_n])
+    ctx.keygen((61, log_n))
+    # the cache holds value 7; m of the pixels have others
+    m = int(round(missing * n))
+    px = np.full(n, 7, dtype=np.uint8)
+    at = np.random.default_rng([log_n, n, m]).permutation(n)[:m]
+    px[at] = 20 + np.arange(m) % 200
+    scan = torch.full((8,), 7, dtype=torch.uint8, device="cuda")
+    cache = ctx.cache_build(P.CKKS_CACHE_VALUE_TOPK, topk=1, zero_pool=4, scan_px=scan, seed=(62, log_n))
+    dev = torch.from_numpy(px).cuda()
+    got = ctx.encrypt_cached(cache, dev, (63, n), 3).data.view(n, -1)
+    plain = ctx.encrypt_pixels(dev, (63, n), 3).data.view(n, -1)
+    torch.cuda.synchronize()
+    miss = torch.from_numpy(px != 7).cuda()
+    assert torch.equal(got[miss], plain[miss])
+    # hits, piece by piece: calls of at most 64 pixels
+    for a in range(0, n, 64):
+        part = ctx.encrypt_cached(cache, dev[a:a + 64].contiguous(), (63, n), 3 + a).data.view(min(64, n - a), -1)
+        assert torch.equal(got[a:a + 64], part), a
+    cache.close()
+    ctx.close()
