@@ -77,8 +77,7 @@ int resolve_params(const ckks_params *p, host::Resolved *r) {
 
 void free_tables(ckks_ctx *c) {
   DevTables &d = c->dev;
-  void *ptrs[] = {d.tw_fwd, d.tw_inv, d.cosj, d.cdt, d.s, d.pk, d.fft_fwd, d.fft_inv,
-                  d.pk_fft, d.s_fft, d.pk_hat, d.s_hat, d.evk, d.evk_hat, c->d_lc};
+  void *ptrs[] = {d.tw_fwd, d.tw_inv, d.cosj, d.cdt, d.s, d.pk, d.fft_fwd, d.pk_hat, d.s_hat, d.evk, d.evk_hat, c->d_lc};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   d = DevTables{};
@@ -436,10 +435,14 @@ int ckks_context_create(const ckks_params *params, int device, ckks_ctx **out) {
   if (e == hipSuccess) e = dev_alloc(&d.cdt, (size_t)kCdtSlots + (1u << kGuideBits) / sizeof(uint64_t));
   if (e == hipSuccess) e = dev_alloc(&d.s, (size_t)N);
   if (e == hipSuccess) e = dev_alloc(&d.pk, (size_t)2 * L * N);
+  // the complex transforms' tables share one allocation
   const size_t M = (size_t)N / 2;
-  for (Cplx **t : {&d.fft_fwd, &d.fft_inv, &d.s_fft})
-    if (e == hipSuccess) e = dev_alloc(t, M);
-  if (e == hipSuccess) e = dev_alloc(&d.pk_fft, (size_t)2 * L * 2 * M);
+  if (e == hipSuccess) e = dev_alloc(&d.fft_fwd, (3 + (size_t)4 * L) * M);
+  if (e == hipSuccess) {
+    d.fft_inv = d.fft_fwd + M;
+    d.s_fft = d.fft_inv + M;
+    d.pk_fft = d.s_fft + M;
+  }
   if (e == hipSuccess) e = dev_alloc(&d.s_hat, (size_t)L * N);
   if (e == hipSuccess) e = dev_alloc(&d.pk_hat, (size_t)2 * L * N);
   if (e != hipSuccess) {
@@ -457,8 +460,8 @@ int ckks_context_create(const ckks_params *params, int device, ckks_ctx **out) {
   if (e == hipSuccess) e = upload(d.cdt, cdt);
   std::vector<double> ff, fi;
   host::fft_tables(r.log_n, ff, fi);
+  ff.insert(ff.end(), fi.begin(), fi.end());
   if (e == hipSuccess) e = upload(reinterpret_cast<double *>(d.fft_fwd), ff);
-  if (e == hipSuccess) e = upload(reinterpret_cast<double *>(d.fft_inv), fi);
   if (e == hipSuccess) e = dev_alloc(&c->d_lc, 1);
   if (e == hipSuccess) e = hipMemcpy(c->d_lc, &c->lc, sizeof(LimbConsts), hipMemcpyHostToDevice);
   if (e == hipSuccess) {

@@ -46,7 +46,7 @@ struct DevTables {
   uint64_t *cdt = nullptr;   // [kCdtSlots], then the guide of 2^kGuideBits bytes
   int64_t *s = nullptr;      // [N] secret key
   uint64_t *pk = nullptr;    // [2][L][N] public key, coefficient domain
-  // Complex transforms (fft.hpp), M = N/2 points each
+  // Complex transforms (fft.hpp), M = N/2 points each, in one allocation at fft_fwd
   Cplx *fft_fwd = nullptr, *fft_inv = nullptr;  // [M] factors
   Cplx *pk_fft = nullptr;    // [2][L][2][M] transforms of the low and high pieces of pk, times 1/M
   Cplx *s_fft = nullptr;     // [M] transform of s, times 1/M

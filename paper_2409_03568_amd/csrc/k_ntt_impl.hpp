@@ -608,52 +608,42 @@ __global__ void __launch_bounds__(1 << (LOGN - LOGR))
 }
 
 // ---------------------------------------------------------------------------
-// Complex transforms of the keys, times 1/M (fft.hpp), value r of thread tid at r T + tid:
-// blockIdx.x = 0: s; 1 + p L + l: the low and high pieces of pk_p in limb l (centered residues).
+// transforms of the keys, by one launch of 7 L + 1 workgroups
 // ---------------------------------------------------------------------------
+// A complex transform, times 1/M (fft.hpp), value r of thread tid at r T + tid: i = -1: s; 2 row +
+// piece: the low or high piece of row p L + l, pk_p in limb l (centered residues).
 template <int LOGN, int RC>
-__global__ void __launch_bounds__(1 << (LOGN - 5)) k_keys_prepare(const LimbConsts *__restrict__ lcp, DevTables dt) {
+__device__ __forceinline__ void prepare_complex(int i, double *lds, const LimbConsts &lc, const DevTables &dt) {
   using F = Fft<LOGN>;
   constexpr double unit = Split<RC>::unit;
-  const LimbConsts &lc = *lcp;
-  extern __shared__ __attribute__((aligned(128))) double lds[];
-  const int tid = threadIdx.x, p = (int)fft_place<LOGN>((unsigned)tid), L = lc.L, row = (int)blockIdx.x - 1;
-  double x[2][2][16];
+  const int tid = threadIdx.x, p = (int)fft_place<LOGN>((unsigned)tid), row = i >> 1;
+  double x[1][2][16];
 #pragma unroll
   for (int r = 0; r < 32; r++) {
     const int j = p + F::T * r;
-    double lo, hi = 0.0;
-    if (row < 0) {
-      lo = (double)dt.s[j];
+    double v;
+    if (i < 0) {
+      v = (double)dt.s[j];
     } else {
-      const double q = lc.q[row % L], w = (double)dt.pk[(size_t)row * 2 * F::M + j];
-      const double c = w > 0.5 * q ? w - q : w;
-      hi = __builtin_rint(c * (1.0 / unit));
-      lo = __builtin_fma(-hi, unit, c);
+      const double q = lc.q[row % lc.L], w = (double)dt.pk[(size_t)row * 2 * F::M + j];
+      const double c = w > 0.5 * q ? w - q : w, hi = __builtin_rint(c * (1.0 / unit));
+      v = i & 1 ? hi : __builtin_fma(-hi, unit, c);
     }
-    x[0][r >> 4][r & 15] = lo;
-    x[1][r >> 4][r & 15] = hi;
+    x[0][r >> 4][r & 15] = v;
   }
-  fft_forward<LOGN, 2>(x, lds, tid, dt.fft_fwd);
-  Cplx *dst = row < 0 ? dt.s_fft : dt.pk_fft + (size_t)row * 2 * F::M;
+  fft_forward<LOGN, 1>(x, lds, tid, dt.fft_fwd);
+  Cplx *dst = i < 0 ? dt.s_fft : dt.pk_fft + (size_t)i * F::M;
 #pragma unroll
-  for (int r = 0; r < 16; r++) {
-    const int at = r * F::T + tid;
-    dst[at] = Cplx{x[0][0][r] * (1.0 / F::M), x[0][1][r] * (1.0 / F::M)};
-    if (row >= 0) dst[F::M + at] = Cplx{x[1][0][r] * (1.0 / F::M), x[1][1][r] * (1.0 / F::M)};
-  }
+  for (int r = 0; r < 16; r++) dst[r * F::T + tid] = Cplx{x[0][0][r] * (1.0 / F::M), x[0][1][r] * (1.0 / F::M)};
 }
 
-// Prime-field transforms of the keys in limb l = blockIdx.x, times N^-1: blockIdx.y = 0: s; 1, 2: pk0,
-// pk1 (for k_encrypt_ntt).
+// Prime-field transforms, times N^-1, in limb l: which = 0: s; 1, 2: pk0, pk1.
 template <int LOGN, int LOGR, int RC>
-__global__ void __launch_bounds__(1 << (LOGN - LOGR)) k_keys_prepare_ntt(const LimbConsts *__restrict__ lcp, DevTables dt) {
+__device__ __forceinline__ void prepare_ntt(int l, int which, double *lds, const LimbConsts &lc, const DevTables &dt) {
   using S = Shape<LOGN, LOGR>;
   using Red = Schedule<LOGN, RC>;
   constexpr int N = S::N, R = S::R, T = S::T;
-  const LimbConsts &lc = *lcp;
-  extern __shared__ __attribute__((aligned(128))) double lds[];
-  const int tid = threadIdx.x, l = blockIdx.x, which = blockIdx.y, L = lc.L;
+  const int tid = threadIdx.x, L = lc.L;
   const double q = lc.q[l], qinv = lc.qinv[l];
   double x[R];
   if (which == 0) {
@@ -670,6 +660,24 @@ __global__ void __launch_bounds__(1 << (LOGN - LOGR)) k_keys_prepare_ntt(const L
 #pragma unroll
   for (int r = 0; r < R; r++)
     dst[elem_index<LOGN, LOGR, S::LAST>(tid, r)] = reduce(mulmod(x[r], lc.ninv[l], q, qinv), q, qinv);
+}
+
+// Workgroups of the prime-field transforms' size, at most 512 threads; a complex transform takes the
+// first T of them.
+template <int LOGN>
+constexpr int kPrepareLogr = LOGN == 14 ? 5 : 4;
+template <int LOGN, int RC>
+__global__ void __launch_bounds__(1 << (LOGN - kPrepareLogr<LOGN>)) __attribute__((amdgpu_waves_per_eu(2)))
+    k_keys_prepare(const LimbConsts *__restrict__ lcp, DevTables dt) {
+  const LimbConsts &lc = *lcp;
+  extern __shared__ __attribute__((aligned(128))) double lds[];
+  const int i = (int)blockIdx.x - 3 * lc.L;
+  if (i < 0) {
+    prepare_ntt<LOGN, kPrepareLogr<LOGN>, RC>((i + 3 * lc.L) % lc.L, (i + 3 * lc.L) / lc.L, lds, lc, dt);
+  } else {
+    if (threadIdx.x >= Fft<LOGN>::T) return;  // whole waves: the barriers below are among the remaining ones
+    prepare_complex<LOGN, RC>(i - 1, lds, lc, dt);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -726,14 +734,10 @@ struct FftLaunch {
     return hipGetLastError();
   }
   static hipError_t prepare(const ckks_ctx *c, hipStream_t st) {
-    hipError_t e = set_lds<k_keys_prepare<LOGN, RC>, B::exchange>();
+    using S = Shape<LOGN, kPrepareLogr<LOGN>>;
+    hipError_t e = set_lds<k_keys_prepare<LOGN, RC>, S::lds_bytes>();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_keys_prepare<LOGN, RC>), dim3(2 * c->lc.L + 1), dim3(T), B::exchange, st, c->d_lc, c->dev);
-    using S = Shape<LOGN, 4>;
-    e = set_lds<k_keys_prepare_ntt<LOGN, 4, RC>, S::lds_bytes>();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_keys_prepare_ntt<LOGN, 4, RC>), dim3(c->lc.L, 3), dim3(S::T), S::lds_bytes,
-                       st, c->d_lc, c->dev);
+    hipLaunchKernelGGL((k_keys_prepare<LOGN, RC>), dim3(7 * c->lc.L + 1), dim3(S::T), S::lds_bytes, st, c->d_lc, c->dev);
     return hipGetLastError();
   }
   template <int LOGR, int LIMBS>
