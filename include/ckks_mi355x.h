@@ -341,12 +341,13 @@ int ckks_stream_sync(ckks_ctx *ctx, void *stream);
 int ckks_stream_status(ckks_ctx *ctx, void *stream);
 
 /* ---- autotuning ----
- * Times the kernels on prime-field transforms (encryption, Sec. 2.2.2, of trial_cts
- * pixels, but at most a few hundred; decryption on limb 0) at each supported register blocking (8,
- * 16 or 32 values per thread) on trial_cts synthetic ciphertexts, and, once
- * ckks_relin_keygen has run, the relinearized product
- * (Sec. 2.2.3) of trial_cts pairs; keeps the fastest width for each kernel on this
- * context, or the present one when the fastest is not 3% faster.  Then times the
+ * Times the kernels on prime-field transforms at each supported register blocking (8, 16 or
+ * 32 values per thread): encryption (Sec. 2.2.2) of as many pixels, up to trial_cts, as still
+ * take that kernel; decryption on limb 0 of trial_cts synthetic ciphertexts together with
+ * batched cache hits, which have its width; and, once ckks_relin_keygen has run, the
+ * relinearized product (Sec. 2.2.3) of trial_cts pairs.  Keeps the fastest width for each on this
+ * context, or the present one when the fastest is not 3% faster or no count takes a kernel
+ * that has widths (encryption at N = 16384: its timings are then INFINITY).  Then times the
  * launch shapes of the HBM-bound kernels: the row-wise
  * kernels (ciphertext addition, Sec. 2.2.3, standing for every row-wise kernel:
  * subtraction, constants, rescaling, radix gather) at 0 (one workgroup per row), 2, 4,
@@ -359,7 +360,7 @@ typedef struct {
   uint32_t encrypt_width, decrypt_width;  /* chosen values per thread */
   uint32_t trial_cts, mul_width;          /* mul_width 0: product not timed (no keys) */
   double encrypt_ms[3], decrypt_ms[3];    /* best of 3 runs: [0] 8, [1] 16, [2] 32 values per thread */
-  double mul_ms[3];                       /* the same for the product (INFINITY if not timed) */
+  double mul_ms[3];                       /* the same for the product (each INFINITY where not timed) */
   uint32_t row_wgs_per_cu, gather_wgs_per_cu; /* chosen launch shapes */
   double row_ms[5];                       /* best of 3 runs at 0, 2, 4, 8, 16 workgroups per CU */
   double gather_ms[5];                    /* best of 3 runs at 2, 4, 8, 16, 32 workgroups per CU */

@@ -356,6 +356,7 @@ int ckks_autotune(ckks_ctx *ctx, uint32_t trial_cts, ckks_tune_report *out) {
   double *dec = nullptr;
   uint64_t *prod = nullptr, *scratch = nullptr;
   uint32_t *meta = nullptr, *hits = nullptr, *counters = nullptr;
+  uint64_t *seg = nullptr;  // one image: its end, its brightness
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t e = hipMalloc(reinterpret_cast<void **>(&px), trial_cts);
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&cts), (uint64_t)trial_cts * ckks_ct_bytes(ctx, L));
@@ -364,6 +365,7 @@ int ckks_autotune(ckks_ctx *ctx, uint32_t trial_cts, ckks_tune_report *out) {
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&meta), (uint64_t)trial_cts * sizeof(uint32_t));
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&hits), (uint64_t)trial_cts * sizeof(uint32_t));
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&counters), kCountersHead * sizeof(uint32_t));
+  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&seg), 2 * sizeof(uint64_t));
   if (e == hipSuccess && ctx->has_relin)
     e = hipMalloc(reinterpret_cast<void **>(&prod), (uint64_t)trial_cts * ckks_ct_bytes(ctx, L));
   if (e == hipSuccess && ctx->has_relin)
@@ -371,25 +373,36 @@ int ckks_autotune(ckks_ctx *ctx, uint32_t trial_cts, ckks_tune_report *out) {
   if (e == hipSuccess) e = hipMemset(px, 0x5a, trial_cts);
   if (e == hipSuccess) e = hipEventCreate(&e0);
   if (e == hipSuccess) e = hipEventCreate(&e1);
-  // Best of three timed runs after one warm-up; `before` runs untimed ahead of each.
-  auto best_ms = [&](auto &&launch, auto &&before) {
-    double best = INFINITY;
-    for (int rep = 0; rep < 4 && e == hipSuccess; rep++) {
-      float ms = 0.f;
-      e = before();
-      if (e == hipSuccess) e = hipEventRecord(e0, nullptr);
-      if (e == hipSuccess) e = launch();
-      if (e == hipSuccess) e = hipEventRecord(e1, nullptr);
-      if (e == hipSuccess) e = hipEventSynchronize(e1);
-      if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-      if (e == hipSuccess && rep) best = fmin(best, ms);
-    }
-    return best;
+  // Best of three timed rounds after a warm-up one, for the candidates i < count that use(i) takes
+  // (INFINITY for the others).  They take turns in each round, so that a drift of the clocks meets
+  // all alike; `before` runs untimed ahead of each launch.
+  auto time_each = [&](int count, double *best, auto &&use, auto &&launch, auto &&before) {
+    for (int i = 0; i < count; i++) best[i] = INFINITY;
+    for (int rep = 0; rep < 4 && e == hipSuccess; rep++)
+      for (int i = 0; i < count && e == hipSuccess; i++) {
+        if (!use(i)) continue;
+        float ms = 0.f;
+        e = before();
+        if (e == hipSuccess) e = hipEventRecord(e0, nullptr);
+        if (e == hipSuccess) e = launch();
+        if (e == hipSuccess) e = hipEventRecord(e1, nullptr);
+        if (e == hipSuccess) e = hipEventSynchronize(e1);
+        if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+        if (e == hipSuccess && rep) best[i] = fmin(best[i], ms);
+      }
   };
   auto nothing = [] { return hipSuccess; };
+  // Width w of the kernels that *logr belongs to, where N allows it.
+  auto width = [&](int *logr) {
+    return [ctx, logr](int w) {
+      if ((ctx->N >> (3 + w)) > 1024) return false;  // more threads than a workgroup holds
+      *logr = 3 + w;
+      return true;
+    };
+  };
   const int keep_enc = ctx->logr_enc, keep_dec = ctx->logr_dec, keep_mul = ctx->logr_mul;
   const int keep_row = ctx->row_wgs, keep_gather = ctx->gather_wgs;
-  double enc_ms[3] = {INFINITY, INFINITY, INFINITY}, dec_ms[3] = {INFINITY, INFINITY, INFINITY};
+  double enc_ms[3] = {INFINITY, INFINITY, INFINITY}, dec_ms[3], hit_ms[3];
   double mul_ms[3] = {INFINITY, INFINITY, INFINITY};
   EncJob job;
   job.px = px;
@@ -398,42 +411,23 @@ int ckks_autotune(ckks_ctx *ctx, uint32_t trial_cts, ckks_tune_report *out) {
   job.seed1 = 0x70u;
   job.out = cts;
   if (e == hipSuccess) e = launch_encrypt(ctx, job, trial_cts, nullptr);
-  // Counts for which the width matters: below two pixels per CU encryption takes the prime-field
-  // kernel where there is one, and at N = 8192 decryption does up to one workgroup per CU.
-  const uint32_t enc_cts = std::min<uint32_t>(trial_cts, 2u * (uint32_t)ctx->num_cus - 1);
-  const uint64_t dec_grid = ctx->prm.log_n == 13 ? (uint64_t)ctx->num_cus : 0;
-  for (int w = 0; w < 3 && e == hipSuccess; w++) {
-    if ((ctx->N >> (3 + w)) > 1024) continue;  // more threads than a workgroup holds
-    ctx->logr_enc = ctx->logr_dec = ctx->logr_mul = 3 + w;
-    job.n = enc_cts;
-    enc_ms[w] = best_ms([&] { return launch_encrypt(ctx, job, enc_cts, nullptr); }, nothing);
-    dec_ms[w] = best_ms(
-        [&] { return launch_decrypt(ctx, cts, trial_cts, (int)L, ctx->scale, dec, 1, nullptr, dec_grid); }, nothing);
-    if (prod)
-      mul_ms[w] = best_ms([&] { return launch_mul(ctx, cts, cts, prod, trial_cts, (int)L, scratch, nullptr); },
-                          nothing);
-  }
-  // another width than the present one has to be faster by more than timings differ: kernels on
-  // complex transforms have no width
-  auto fastest = [](const double (&ms)[3], int keep) {
-    int best = keep;
-    for (int w = 0; w < 3; w++)
-      if (ms[w] < (best == keep ? 0.97 : 1.0) * ms[best]) best = w;
-    return best;
-  };
-  const int be = fastest(enc_ms, keep_enc - 3), bd = fastest(dec_ms, keep_dec - 3), bm = fastest(mul_ms, keep_mul - 3);
-  ctx->logr_enc = 3 + be;
-  ctx->logr_dec = 3 + bd;
-  ctx->logr_mul = prod ? 3 + bm : keep_mul;
-  // Launch shapes.  The row-wise kernels are timed on the addition of the trial
-  // ciphertexts; the gather on a synthetic all-hit job: 16 entries and 2 pool members
-  // taken from the trial ciphertexts (canonical residues), every ciphertext a hit.
-  static const int kRow[5] = {0, 2, 4, 8, 16}, kGather[5] = {2, 4, 8, 16, 32};
-  double row_ms[5], gather_ms[5];
-  for (int i = 0; i < 5; i++) {
-    ctx->row_wgs = kRow[i];
-    row_ms[i] = best_ms([&] { return launch_add_sub(ctx, cts, cts, gout, trial_cts, (int)L, false, nullptr); }, nothing);
-  }
+  if (e == hipSuccess)
+    e = hipMemcpy(gout, cts, (uint64_t)trial_cts * ckks_ct_bytes(ctx, L), hipMemcpyDeviceToDevice);
+  // Encryption: the most pixels that the kernel with widths takes, if it takes any; otherwise the
+  // present width stays, since timings of one and the same kernel differ by chance alone.
+  const int log_n = ctx->prm.log_n;
+  const uint64_t cus = (uint64_t)ctx->num_cus;
+  job.n = trial_cts;
+  while (job.n && encrypt_kernel(log_n, (int)L, job.n, cus) != kEncPrime) job.n--;
+  if (job.n)
+    time_each(3, enc_ms, width(&ctx->logr_enc), [&] { return launch_encrypt(ctx, job, job.n, nullptr); }, nothing);
+  // Decryption, on as many workgroups as still take the kernel with widths, and the kernel of
+  // batched cache hits, whose width is decryption's: an all-hit job of 16 entries and 2 pool
+  // members taken from the trial ciphertexts (canonical residues).
+  uint64_t dec_grid = trial_cts;
+  while (dec_grid > 1 && decrypt_complex(log_n, ctx->rc, 1, dec_grid, cus)) dec_grid--;
+  time_each(3, dec_ms, width(&ctx->logr_dec),
+            [&] { return launch_decrypt(ctx, cts, trial_cts, (int)L, ctx->scale, dec, 1, nullptr, dec_grid); }, nothing);
   const uint32_t n_ent = std::min<uint32_t>(16, trial_cts), n_pool = std::min<uint32_t>(2, trial_cts);
   std::vector<uint32_t> h_meta(trial_cts), h_hits(trial_cts), h_counters(kCountersHead, 0);
   for (uint32_t i = 0; i < trial_cts; i++) {
@@ -441,20 +435,68 @@ int ckks_autotune(ckks_ctx *ctx, uint32_t trial_cts, ckks_tune_report *out) {
     h_hits[i] = i;
   }
   h_counters[1] = trial_cts;
+  const uint64_t one_image = trial_cts;
+  const double no_brightness = 0.0;
   if (e == hipSuccess) e = hipMemcpy(meta, h_meta.data(), trial_cts * sizeof(uint32_t), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(hits, h_hits.data(), trial_cts * sizeof(uint32_t), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemcpy(seg, &one_image, sizeof(one_image), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemcpy(seg + 1, &no_brightness, sizeof(no_brightness), hipMemcpyHostToDevice);
+  auto all_hits = [&] {
+    return hipMemcpy(counters, h_counters.data(), kCountersHead * sizeof(uint32_t), hipMemcpyHostToDevice);
+  };
+  FusedJob batch;
+  batch.n = trial_cts;
+  batch.out = prod ? prod : gout;
+  batch.counters = counters;
+  batch.hits = hits;
+  batch.meta = meta;
+  batch.entries = batch.pool = cts;
+  batch.seg_end = seg;
+  batch.seg_b = reinterpret_cast<const double *>(seg + 1);
+  batch.n_seg = 1;
+  batch.cursor = counters + 2;
+  batch.dec_out = dec;
+  batch.inv_scale = 1.0;
+  batch.ring = trial_cts;
+  // (the product's second factor is in gout: timed before the hits write there)
+  if (prod)
+    time_each(3, mul_ms, width(&ctx->logr_mul),
+              [&] { return launch_mul(ctx, cts, gout, prod, trial_cts, (int)L, scratch, nullptr); }, nothing);
+  time_each(3, hit_ms, width(&ctx->logr_dec), [&] { return launch_cached_fused(ctx, batch, false, nullptr); }, all_hits);
+  // another width than the present one has to be faster by more than timings differ
+  auto fastest = [](const double (&ms)[3], int keep) {
+    int best = keep;
+    for (int w = 0; w < 3; w++)
+      if (ms[w] < (best == keep ? 0.97 : 1.0) * ms[best]) best = w;
+    return best;
+  };
+  double both_ms[3];
+  for (int w = 0; w < 3; w++) both_ms[w] = dec_ms[w] + hit_ms[w];
+  ctx->logr_enc = 3 + fastest(enc_ms, keep_enc - 3);
+  ctx->logr_dec = 3 + fastest(both_ms, keep_dec - 3);
+  ctx->logr_mul = 3 + fastest(mul_ms, keep_mul - 3);
+  // Launch shapes.  The row-wise kernels are timed on the addition of the trial
+  // ciphertexts; the gather on the all-hit job.
+  static const int kRow[5] = {0, 2, 4, 8, 16}, kGather[5] = {2, 4, 8, 16, 32};
+  double row_ms[5], gather_ms[5];
+  time_each(
+      5, row_ms,
+      [&](int i) {
+        ctx->row_wgs = kRow[i];
+        return true;
+      },
+      [&] { return launch_add_sub(ctx, cts, cts, gout, trial_cts, (int)L, false, nullptr); }, nothing);
   ckks_cache fake;
   fake.ctx = ctx;
   fake.entries = cts;
   fake.pool_cts = cts;
-  for (int i = 0; i < 5; i++) {
-    ctx->gather_wgs = kGather[i];
-    gather_ms[i] = best_ms(
-        [&] {
-          return launch_value_gather(ctx, &fake, meta, counters, hits, trial_cts, gout, nullptr, nullptr, 0);
-        },
-        [&] { return hipMemcpy(counters, h_counters.data(), kCountersHead * sizeof(uint32_t), hipMemcpyHostToDevice); });
-  }
+  time_each(
+      5, gather_ms,
+      [&](int i) {
+        ctx->gather_wgs = kGather[i];
+        return true;
+      },
+      [&] { return launch_value_gather(ctx, &fake, meta, counters, hits, trial_cts, gout, nullptr, nullptr, 0); }, all_hits);
   int br = 0, bg = 0;
   for (int i = 1; i < 5; i++) {
     if (row_ms[i] < row_ms[br]) br = i;
@@ -463,7 +505,7 @@ int ckks_autotune(ckks_ctx *ctx, uint32_t trial_cts, ckks_tune_report *out) {
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   for (void *ptr : {(void *)px, (void *)cts, (void *)gout, (void *)dec, (void *)prod, (void *)scratch, (void *)meta,
-                    (void *)hits, (void *)counters})
+                    (void *)hits, (void *)counters, (void *)seg})
     if (ptr) (void)hipFree(ptr);
   if (e != hipSuccess) {
     ctx->logr_enc = keep_enc;
