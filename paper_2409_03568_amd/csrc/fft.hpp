@@ -441,19 +441,42 @@ __device__ __forceinline__ void fft_inverse(double (&x)[NA][2][16], double *lds,
 }
 
 // Congruent to hi 2^h + w mod q for integer-valued hi (|hi| 2^h < 2^66) and w (|w| < 2^51,
-// w + the result below 2^53): |result| <= q/2 + 1.  qinv_u = 2^h / q.  H - c q is an integer
-// below 2^53, so the fused multiply-add forms it exactly.
+// w + the result below 2^53).  qinv_u = 2^h / q.  H - c q is an integer below 2^53, so the fused
+// multiply-add forms it exactly.  The quotient, of magnitude up to N, is rounded from a value off by
+// up to N 2^-51, so |result| <= q/2 + N q 2^-51 + 1: past q/2 by up to 2^12 at N = 8192 and 50 bits.
+// (wrap_center and encrypt_residue take anything below 3q/2 and q.)
 CKKS_HD double fft_combine(double hi, double w, double unit, double q, double qinv, double qinv_u) {
   const double c = __builtin_rint(__builtin_fma(hi, qinv_u, w * qinv));
   return __builtin_fma(-c, q, hi * unit) + w;
 }
 
-// Centered residue, in (-q/2, q/2], of r with |r| <= q/2 + 1 (q odd).
+// Centered residue, in (-q/2, q/2], of r with |r| < 3q/2 (q odd).
 CKKS_HD double wrap_center(double r, double q) {
   return __builtin_fabs(r) > 0.5 * q ? r - __builtin_copysign(q, r) : r;
 }
 
 // Canonical residue of r in (-q, q).
 CKKS_HD double wrap_positive(double r, double q) { return r < 0.0 ? r + q : r; }
+
+// Last step of a row of encryption: the canonical residue of hi 2^h + lo - b, hi the rounded high
+// piece of v pk, lo the low one plus everything added to it and the errors' offset b, not rounded yet.
+template <int LOGN, int RC, int POLY>
+CKKS_HD uint64_t encrypt_residue(double hi, double lo, double q, double qinv, double qinv_u, double b) {
+  constexpr double unit = Split<RC>::unit;
+  double c;  // c0 or c1, plus b, in (-q, q)
+  if constexpr (RC == 0 && LOGN <= 12) {
+    // |v pk| <= N q/2 <= 2^51: the sum of the pieces is exact
+    const double y = __builtin_fma(hi, unit, __builtin_rint(lo));
+    c = __builtin_fma(-__builtin_rint(y * qinv), q, y);
+  } else if constexpr (RC == 1 && POLY == 1) {
+    // |low piece| <= N 2^24 + 2B < q/2 (q > 2^40): the high piece alone gives the quotient
+    c = __builtin_fma(-__builtin_rint(hi * qinv_u), q, hi * unit) + lo;
+  } else {
+    c = fft_combine(hi, lo, unit, q, qinv, qinv_u);
+  }
+  // without b, wrapped to [0, q) and rounded by the addition of 2^52: before it the low piece
+  // was off its integer by under 2^-5, and the sums of magnitudes up to 2^50 by under 2^-1.3
+  return __builtin_bit_cast(uint64_t, c + (c < b - 0.5 ? (kTwo52 - b) + q : kTwo52 - b)) - kTwo52Bits;
+}
 
 }  // namespace ckks

@@ -13,7 +13,7 @@ namespace ckks {
 //   x0 = [d_0]_{q_0} and k = [(d_1 - x0) q_0^-1]_{q_1}, exact while |x_j| < q_0 q_1 / 2
 //   (the sum is formed in FP64, so a lift beyond 2^53 is rounded to 53 bits).
 // ---------------------------------------------------------------------------
-// x = c0 + x s mod q, |x| <= q/2 + 1, from integer-valued x in [0, 2^52) (c1; register r:
+// x = c0 + x s mod q, |x| as of fft_combine, from integer-valued x in [0, 2^52) (c1; register r:
 // coefficient p + T r) and c0(r), the canonical coefficient of the same register.  load(0) and
 // load(1) run before the last pass and after it, for the c0 of values 0..7 and 8..15.
 template <int LOGN, int RC, class LOAD, class C0>
@@ -77,7 +77,7 @@ __device__ __forceinline__ void load_row(double (&x)[32], const uint64_t *row) {
   for (int r = 0; r < 32; r++) x[r] = u64_to_f64(__builtin_nontemporal_load(row_at(row + Fft<LOGN>::T * r, p)));
 }
 
-// d = c0 + c1 s mod q, |d| <= q/2 + 1, in coefficient order: c1 in x (consumed), c0 in memory.
+// d = c0 + c1 s mod q, |d| as of fft_combine, in coefficient order: c1 in x (consumed), c0 in memory.
 template <int LOGN, int RC>
 __device__ __forceinline__ void decrypt_limb(double (&x)[32], const uint64_t *c0, double *lds, double q, double qinv,
                                              const DevTables &dt) {
@@ -179,7 +179,7 @@ __global__ void __launch_bounds__(1 << (LOGN - 5)) __attribute__((amdgpu_waves_p
       decrypt_limb<LOGN, RC>(y, c0 + N, lds, q1, q1inv, dt);
 #pragma unroll
       for (int r = 0; r < 32; r++) {
-        // |y| <= q_1/2 + 1 and |x| <= q_0/2: the difference stays below 2^51
+        // |y| < q_1/2 + 2^13 and |x| <= q_0/2: the difference stays below 2^51
         const double k = center(mulmod(y[r] - x[r], w, q1, q1inv), q1, q1inv);
         x[r] = __builtin_fma(k, q, x[r]);
         computed_here(x[r]);

@@ -311,20 +311,7 @@ __device__ __forceinline__ void encrypt_row(RowHalf &res, uint64_t *before, uint
       }
       const double lo = __builtin_fma(tr, x[0][0][r], __builtin_fma(ti, x[0][1][r], add));
       const double hi = __builtin_rint(__builtin_fma(tr, x[1][0][r], ti * x[1][1][r]));
-      double c;  // c0 or c1, plus B, in (-q, q)
-      if constexpr (RC == 0 && LOGN <= 12) {
-        // |v pk| <= N q/2 <= 2^51: the sum of the pieces is exact
-        const double y = __builtin_fma(hi, unit, __builtin_rint(lo));
-        c = __builtin_fma(-__builtin_rint(y * qinv), q, y);
-      } else if constexpr (RC == 1 && POLY == 1) {
-        // |low piece| <= N 2^24 + 2B < q/2 (q > 2^40): the high piece alone gives the quotient
-        c = __builtin_fma(-__builtin_rint(hi * qinv_u), q, hi * unit) + lo;
-      } else {
-        c = fft_combine(hi, lo, unit, q, qinv, qinv_u);
-      }
-      // without B, wrapped to [0, q) and rounded by the addition of 2^52: before it the low piece
-      // was off its integer by under 2^-5, and the sums of magnitudes up to 2^50 by under 2^-1.3
-      uint64_t w = __builtin_bit_cast(uint64_t, c + (c < b - 0.5 ? (kTwo52 - b) + q : kTwo52 - b)) - kTwo52Bits;
+      uint64_t w = encrypt_residue<LOGN, RC, POLY>(hi, lo, q, qinv, qinv_u, b);
       computed_here(w);
       res.w[im][r % 8] = w;
     }

@@ -84,8 +84,9 @@ def test_combine_near_half_quotients(emu, oracle_mod, log_n, bits):
     rng = np.random.default_rng([log_n, bits])
     top = N << max(bits - h, 1)                                   # |hi| of a canonical residue's high piece
     k = np.concatenate([rng.integers(-N, N, 4000), np.array([N - 1, N - 2, 1 - N, 0, -1])])
-    off = rng.integers(-3, 4, len(k))
-    total = [int(a) * q + q // 2 + int(b) for a, b in zip(k, off)]  # (k + 1/2) q, to a few units
+    reach = max(3, int(N * q * 2.0**-50))                         # twice the bound's excess over q/2
+    off = rng.integers(-reach, reach + 1, len(k))
+    total = [int(a) * q + q // 2 + int(b) for a, b in zip(k, off)]  # next to (k + 1/2) q
     hi = np.array([min(max((t + (1 << (h - 1))) >> h, -top), top) for t in total], dtype=np.int64)
     w = np.array([t - (int(x) << h) for t, x in zip(total, hi)], dtype=object)
     keep = [abs(int(x)) < N << h for x in w]
