@@ -332,6 +332,7 @@ hipError_t launch_cached_fused(const ckks_ctx *c, const FusedJob &job, bool miss
 hipError_t launch_keygen(const ckks_ctx *c, uint64_t seed0, uint64_t seed1, hipStream_t stream);
 hipError_t launch_keys_prepare(const ckks_ctx *c, hipStream_t stream);
 hipError_t launch_encrypt(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t stream);
+hipError_t launch_encrypt_prime(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t stream);  // N <= 8192
 // limbs = 1: decode the centered residue of limb 0; limbs = 2 (level >= 2): decode the
 // centered CRT lift of limbs 0 and 1.  max_grid (0 = no bound): at most this many
 // workgroups, each taking every max_grid-th ciphertext.

@@ -149,7 +149,7 @@ __device__ __forceinline__ DecItem dec_item(const DecJob &job, uint64_t i) {
 }
 
 // Registers are budgeted for two waves per SIMD; the two-limb form holds limb 0's values across
-// limb 1's transforms (40 registers spilled; with the limbs side by side in one workgroup of
+// limb 1's transforms (32 registers spilled; with the limbs side by side in one workgroup of
 // twice the threads nothing is spilled, but all of them wait for each other: 8.5 against 6.8 ms
 // per 65,536 at N = 8192).  LOGR: the order of the decoded sum only.
 template <int LOGN, int LOGR, int RC, int LIMBS>

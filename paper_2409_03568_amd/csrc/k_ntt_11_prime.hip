@@ -1,0 +1,3 @@
+// Kernels of the NTT path for N = 2^11: encryption through prime-field transforms (see k_ntt_impl.hpp).
+#include "k_ntt_impl.hpp"
+CKKS_DEFINE_RING_PRIME(11)

@@ -17,6 +17,9 @@ CKKS_DECLARE_RING(11)
 CKKS_DECLARE_RING(12)
 CKKS_DECLARE_RING(13)
 CKKS_DECLARE_RING(14)
+hipError_t launch_encrypt_prime_11(const ckks_ctx *, const EncJob &, uint64_t, hipStream_t);
+hipError_t launch_encrypt_prime_12(const ckks_ctx *, const EncJob &, uint64_t, hipStream_t);
+hipError_t launch_encrypt_prime_13(const ckks_ctx *, const EncJob &, uint64_t, hipStream_t);
 
 #define CKKS_RING_SWITCH(FN, ...)                      \
   switch (c->prm.log_n) {                              \
@@ -29,6 +32,14 @@ CKKS_DECLARE_RING(14)
 
 hipError_t launch_encrypt(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t stream) {
   CKKS_RING_SWITCH(launch_encrypt, job, grid, stream)
+}
+hipError_t launch_encrypt_prime(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t stream) {
+  switch (c->prm.log_n) {
+    case 11: return launch_encrypt_prime_11(c, job, grid, stream);
+    case 12: return launch_encrypt_prime_12(c, job, grid, stream);
+    case 13: return launch_encrypt_prime_13(c, job, grid, stream);
+    default: return hipErrorInvalidValue;
+  }
 }
 hipError_t launch_cached_fused(const ckks_ctx *c, const FusedJob &job, bool misses, hipStream_t stream) {
   CKKS_RING_SWITCH(launch_cached_fused, job, misses, stream)

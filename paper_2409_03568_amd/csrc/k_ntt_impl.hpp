@@ -405,11 +405,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
 // The same through prime-field transforms, for N <= 8192: x = NTT(v) per limb, c0 =
 // INTT(x pk0^) + e0 + m, c1 = INTT(x pk1^) + e1.  N/8 threads per ciphertext where the complex
 // transforms have N/32, so it has the lower latency where whole ciphertexts just fill the device
-// (encrypt_kernel in routes.hpp).
+// (encrypt_kernel in routes.hpp).  Compiled in units of its own, which a program that never takes it
+// does not load.
 // ---------------------------------------------------------------------------
-template <int LOGN>
-constexpr bool kEncryptNtt = LOGN <= 13;
-
 // One limb of the encryption of the current item, by the whole workgroup (the samples are drawn: in
 // smpl or, where they do not fit LDS, in smp).  With KEEP the canonical values of c0 and c1 are also
 // returned in k0 and k1 (first-pass layout: register r holds coefficient tid + T r).
@@ -839,6 +837,27 @@ struct Launch {
   }
 };
 
+// The compiled form of an encryption kernel that a job takes: f(EncForm<mode, bright>).
+template <int MODE, bool BRIGHT>
+struct EncForm {
+  static constexpr int mode = MODE;
+  static constexpr bool bright = BRIGHT;
+};
+template <typename F>
+static hipError_t encrypt_modes(const EncJob &job, F f) {
+  const bool bright = job.seg_b != nullptr;
+  if (job.vals || job.ts) {
+    if (!job.vals || !job.ts || bright) return hipErrorInvalidValue;
+    return f(EncForm<kEncEntries, false>{});
+  }
+  if (job.list) {
+    if (!job.list_count) return hipErrorInvalidValue;
+    return bright ? f(EncForm<kEncList, true>{}) : f(EncForm<kEncList, false>{});
+  }
+  if (job.list_count) return hipErrorInvalidValue;
+  return bright ? f(EncForm<kEncPixels, true>{}) : f(EncForm<kEncPixels, false>{});
+}
+
 // All launchers of one ring degree, selecting the thread shape (where there is a choice) and the
 // class of the primes (c->rc) at run time.
 template <int LOGN>
@@ -856,30 +875,27 @@ struct RingLaunch {
     if (logr == 5) return c->rc ? f(Launch<LOGN, 5, 1>{}) : f(Launch<LOGN, 5, 0>{});
     return hipErrorInvalidValue;
   }
-  template <int MODE, bool BRIGHT>
-  static hipError_t encrypt_as(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {
+  static hipError_t encrypt(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {
     if (job.n == 0) return hipSuccess;
     const int kernel = job.kernel >= 0 ? job.kernel : encrypt_kernel(LOGN, c->lc.L, job.n, (uint64_t)c->num_cus);
-    if (kernel == kEncSplit && job.n <= grid)
-      return pick(c, [&](auto L) { return decltype(L)::template encrypt_few<MODE, BRIGHT>(c, job, st); });
-    if constexpr (kEncryptNtt<LOGN>)
-      if (kernel == kEncPrime)
-        return pick(c, c->logr_enc,
-                    [&](auto L) { return decltype(L)::template encrypt_as<MODE, BRIGHT>(c, job, grid, st); });
-    return pick(c, [&](auto L) { return decltype(L)::template encrypt_as<MODE, BRIGHT>(c, job, grid, st); });
+    if (kernel == kEncPrime && LOGN <= 13) return launch_encrypt_prime(c, job, grid, st);
+    const bool split = kernel == kEncSplit && job.n <= grid;
+    return encrypt_modes(job, [&](auto M) {
+      return pick(c, [&](auto L) {
+        using K = decltype(L);
+        using E = decltype(M);
+        return split ? K::template encrypt_few<E::mode, E::bright>(c, job, st)
+                     : K::template encrypt_as<E::mode, E::bright>(c, job, grid, st);
+      });
+    });
   }
-  static hipError_t encrypt(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {
-    const bool bright = job.seg_b != nullptr;
-    if (job.vals || job.ts) {
-      if (!job.vals || !job.ts || bright) return hipErrorInvalidValue;
-      return encrypt_as<kEncEntries, false>(c, job, grid, st);
-    }
-    if (job.list) {
-      if (!job.list_count) return hipErrorInvalidValue;
-      return bright ? encrypt_as<kEncList, true>(c, job, grid, st) : encrypt_as<kEncList, false>(c, job, grid, st);
-    }
-    if (job.list_count) return hipErrorInvalidValue;
-    return bright ? encrypt_as<kEncPixels, true>(c, job, grid, st) : encrypt_as<kEncPixels, false>(c, job, grid, st);
+  static hipError_t encrypt_prime(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {
+    return encrypt_modes(job, [&](auto M) {
+      return pick(c, c->logr_enc, [&](auto L) {
+        using E = decltype(M);
+        return decltype(L)::template encrypt_as<E::mode, E::bright>(c, job, grid, st);
+      });
+    });
   }
   static hipError_t decrypt(const ckks_ctx *c, const DecJob &job, int limbs, uint64_t grid, hipStream_t st) {
     if constexpr (kDecryptFft<LOGN>)
@@ -895,7 +911,8 @@ struct RingLaunch {
 }  // namespace ckks
 
 // Define the per-ring-degree launcher entry points.  Each ring degree's kernels are spread
-// over three translation units (k_ntt_<LOGN>_{enc,mul,fused}.hip) so they compile in parallel.
+// over four translation units (k_ntt_<LOGN>_{enc,prime,mul,fused}.hip) so they compile in parallel
+// and load when first used.
 #define CKKS_DEFINE_RING_ENC(LOGN)                                                                                  \
   namespace ckks {                                                                                                  \
   hipError_t launch_encrypt_##LOGN(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {           \
@@ -909,6 +926,13 @@ struct RingLaunch {
   }                                                                                                                 \
   hipError_t launch_decrypt_##LOGN(const ckks_ctx *c, const DecJob &job, int limbs, uint64_t grid, hipStream_t st) { \
     return RingLaunch<LOGN>::decrypt(c, job, limbs, grid, st);                                                      \
+  }                                                                                                                 \
+  }
+
+#define CKKS_DEFINE_RING_PRIME(LOGN)                                                                                \
+  namespace ckks {                                                                                                  \
+  hipError_t launch_encrypt_prime_##LOGN(const ckks_ctx *c, const EncJob &job, uint64_t grid, hipStream_t st) {     \
+    return RingLaunch<LOGN>::encrypt_prime(c, job, grid, st);                                                       \
   }                                                                                                                 \
   }
 
