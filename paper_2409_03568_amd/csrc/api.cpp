@@ -215,9 +215,23 @@ hipError_t encrypt_cached_ws(const ckks_ctx *ctx, const ckks_cache *cache, const
   job.out = out;
   if (cache->kind == CKKS_CACHE_VALUE_FULL)  // every value is cached: no misses
     return launch_value_gather(ctx, cache, meta, counters, hits, n, out, nullptr, st);
-  if (!concurrent || !ctx->aux) {
+  const bool beside = concurrent && ctx->aux;
+  const MissRoute r = miss_route(ctx->prm.log_n, beside, n, (uint64_t)ctx->num_cus);
+  const uint64_t grid = std::min<uint64_t>(n, kListGrid);
+  auto encrypt_misses = [&](hipStream_t on) {
+    hipError_t f = hipSuccess;
+    if (r.few_below || r.few_share) {
+      job.gate = MissGate{kFewMisses, r.few_below, r.few_share};
+      job.kernel = r.few;
+      f = launch_encrypt(ctx, job, r.few_grid ? r.few_grid : grid, on);
+      job.gate.turn = kManyMisses;
+    }
+    job.kernel = r.many;
+    return f == hipSuccess ? launch_encrypt(ctx, job, grid, on) : f;
+  };
+  if (!beside) {
     e = launch_value_gather(ctx, cache, meta, counters, hits, n, out, nullptr, st);
-    return e == hipSuccess ? launch_encrypt(ctx, job, std::min<uint64_t>(n, kListGrid), st) : e;
+    return e == hipSuccess ? encrypt_misses(st) : e;
   }
   // The misses (compute-bound full encryptions) run on the auxiliary stream beside the hit
   // gather (bound by HBM writes).  The gather's grid is bounded so that it leaves the CUs room for
@@ -228,15 +242,7 @@ hipError_t encrypt_cached_ws(const ckks_ctx *ctx, const ckks_cache *cache, const
   if (e == hipSuccess) e = hipEventCreateWithFlags(&join, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventRecord(fork, st);
   if (e == hipSuccess) e = hipStreamWaitEvent(ctx->aux, fork, 0);
-  const MissRoute r = miss_route(ctx->prm.log_n, n, (uint64_t)ctx->num_cus);
-  if (r.few_share) {
-    job.gate = MissGate{kFewMisses, 0, r.few_share};
-    job.kernel = r.few;
-    if (e == hipSuccess) e = launch_encrypt(ctx, job, r.few_grid ? r.few_grid : std::min<uint64_t>(n, kListGrid), ctx->aux);
-    job.gate.turn = kManyMisses;
-  }
-  job.kernel = r.many;
-  if (e == hipSuccess) e = launch_encrypt(ctx, job, std::min<uint64_t>(n, kListGrid), ctx->aux);
+  if (e == hipSuccess) e = encrypt_misses(ctx->aux);
   if (e == hipSuccess) e = hipEventRecord(join, ctx->aux);
   if (e == hipSuccess)
     e = launch_value_gather(ctx, cache, meta, counters, hits, n, out, nullptr, st,

@@ -69,12 +69,13 @@ inline bool decrypt_complex(int log_n, int prime_class, int limbs, uint64_t n, u
   return log_n == 13 && n > per_cu * cus;
 }
 
-// How the misses of a value cache among n pixels are encrypted, beside the gather of the hits on
-// another stream.  Complex encryptions fill a CU's registers, so where they come first they hold up
-// the gather: few misses take fewer workgroups or the prime-field kernel, many the whole device.  Which it
-// is the device decides, by the misses being below one in `few_share` of the hits (0: not asked,
-// `many` takes any).  few_grid: workgroups (0: as for many).  In us, misses being 1 in 6 / 1 in 3 or
-// 2 in 5 / 3 in 4 of the pixels:
+// How the misses of a value cache among n pixels are encrypted: beside the gather of the hits on
+// another stream, or after it.  Complex encryptions fill a CU's registers, so where they come first
+// they hold up a gather beside them, and alone they have the longer latency while they are few: few
+// misses take fewer workgroups or the prime-field kernel, many the whole device.  Which it
+// is the device decides, by the misses being below `few_below` plus one in `few_share` of the hits
+// (both 0: not asked, `many` takes any).  few_grid: workgroups (0: as for many).
+// Beside the gather, in us, misses being 1 in 6 / 1 in 3 or 2 in 5 / 3 in 4 of the pixels:
 //   N = 2048, 10,000 pixels: prime-field, 1 per CU 302 / 441 / 741, 2 per CU 312 / 323 / 523,
 //                            unbounded 369 / 347 / 445; complex 418 / 433 / 481
 //             65,536 pixels: prime-field, 1 per CU 1422 / 2580 / 4478, 2 per CU 1318 / 1944 / 3164,
@@ -86,17 +87,26 @@ inline bool decrypt_complex(int log_n, int prime_class, int limbs, uint64_t n, u
 //             65,536 pixels: complex, 1 per CU 7025 / 11883 / 19574, unbounded 6761 / 10037 / 14817
 //   1,024 pixels, prime-field unbounded against complex: N = 2048 109 / 112 / 123 against 144 / 142 / 148,
 //   N = 4096 134 / 137 / 169 against 148 / 163 / 191, N = 8192 217 / 270 / 357 against 206 / 224 / 310
+//   289 pixels in tiles, N = 8192: prime-field 281, complex 302
+// After it, prime-field / complex, 1 in 6 missing: N = 4096, 1,000 pixels 181 / 214; N = 8192, 300
+// pixels 181 / 193, 1,000 pixels 282 / 292.
 struct MissRoute {
-  uint32_t few_share;
+  uint32_t few_below, few_share;
   int few, many;      // EncKernel, -1: by n
   uint64_t few_grid;
 };
-inline MissRoute miss_route(int log_n, uint64_t n, uint64_t cus) {
-  if (log_n == 14 || n <= (log_n == 13 ? 4 : 1) * cus) return MissRoute{0, -1, -1, 0};
-  if (log_n == 13) return MissRoute{2, kEncComplex, kEncComplex, cus};
-  if (n <= 4 * cus) return MissRoute{0, kEncPrime, kEncPrime, 0};
-  if (log_n == 12) return MissRoute{1, kEncPrime, kEncComplex, 0};
-  return MissRoute{2, kEncPrime, kEncPrime, (n < 128 * cus ? 1 : 2) * cus};
+inline MissRoute miss_route(int log_n, bool beside, uint64_t n, uint64_t cus) {
+  constexpr MissRoute by_n{0, 0, -1, -1, 0}, prime{0, 0, kEncPrime, kEncPrime, 0};
+  if (log_n == 14 || n <= (beside ? cus : cus / 2)) return by_n;
+  if (n <= 2 * cus || (log_n < 13 && n <= 4 * cus)) return prime;
+  if (beside) {
+    if (log_n == 13) return n <= 4 * cus ? by_n : MissRoute{0, 2, kEncComplex, kEncComplex, cus};
+    if (log_n == 12) return MissRoute{0, 1, kEncPrime, kEncComplex, 0};
+    return MissRoute{0, 2, kEncPrime, kEncPrime, (n < 128 * cus ? 1 : 2) * cus};
+  }
+  if (log_n == 13) return MissRoute{(uint32_t)cus + 1, 0, kEncPrime, kEncComplex, cus};
+  if (log_n == 11 || n < 12 * cus) return prime;
+  return MissRoute{12 * (uint32_t)cus, 0, kEncPrime, kEncComplex, 0};
 }
 
 // How the misses of a batch (every pixel without a cache) are encrypted and decrypted: by the

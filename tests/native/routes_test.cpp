@@ -83,16 +83,20 @@ static void decryption() {
 }
 
 static void cached_misses() {
-  for (int log_n = 11; log_n <= 14; log_n++)
-    for (uint64_t n : {1ull, 256ull, 1024ull, 1025ull, 4000ull, 65536ull}) {
-      const MissRoute r = miss_route(log_n, n, 256);
-      // complex encryptions of the whole device beside the gather only for many misses
-      if (r.few_share) CHECK(r.few != kEncComplex || r.few_grid == 256);
-      if (r.few_share) CHECK(n > 1024 && log_n < 14);
-      if (log_n == 14) CHECK(r.many < 0);  // kernels that are compiled
-      if (log_n == 11 && n > 256) CHECK(r.many == kEncPrime);
-      if (log_n == 12 && n > 1024) CHECK(r.few == kEncPrime && r.many == kEncComplex);
-    }
+  for (bool beside : {false, true})
+    for (int log_n = 11; log_n <= 14; log_n++)
+      for (uint64_t n : {1ull, 128ull, 256ull, 289ull, 512ull, 1024ull, 1025ull, 4000ull, 65536ull}) {
+        const MissRoute r = miss_route(log_n, beside, n, 256);
+        const bool asked = r.few_below || r.few_share;
+        if (log_n == 14) CHECK(!asked && r.many < 0);  // kernels that are compiled
+        if (asked) CHECK(n > 512 && log_n < 14);
+        // complex encryptions of the whole device beside the gather only for many misses
+        if (asked && beside) CHECK(r.few != kEncComplex || r.few_grid == 256);
+        // after it few take the kernel of the lower latency
+        if (asked && !beside) CHECK(r.few == kEncPrime && r.many == kEncComplex);
+        if (log_n < 14 && n > 256 && n <= 512) CHECK(r.many == kEncPrime);
+        if (log_n == 11 && n > 256) CHECK(r.many == kEncPrime);
+      }
 }
 
 int main() {

@@ -41,3 +41,37 @@ def test_every_share_of_misses(log_n, n, missing):
         assert torch.equal(got[a:a + 64], part), a
     cache.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("log_n", [11, 12, 13, 14])
+@pytest.mark.parametrize("n", [100, 300, 600, 3100])
+@pytest.mark.parametrize("missing", [0.02, 0.5, 1.0])
+def test_without_allocation(log_n, n, missing):
+    """The entry point without allocations encrypts the misses after the gather, by lines of its own;
+    its ciphertexts equal those of the one that does both at once."""
+    import ctypes as C
+
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2409_03568_amd as P
+
+    print("[gpu] misses without allocation N=2^%d, %d pixels, %.2f missing" % (log_n, n, missing), flush=True)
+    ctx = P.Context(log_n, *RINGS[log_n])
+    ctx.keygen((64, log_n))
+    m = int(round(missing * n))
+    px = np.full(n, 7, dtype=np.uint8)
+    px[np.random.default_rng([log_n, n, m]).permutation(n)[:m]] = 20
+    scan = torch.full((8,), 7, dtype=torch.uint8, device="cuda")
+    cache = ctx.cache_build(P.CKKS_CACHE_VALUE_TOPK, topk=1, zero_pool=4, scan_px=scan, seed=(65, log_n))
+    dev, out = torch.from_numpy(px).cuda(), ctx.empty(n)
+    b = out.out_batch()
+    rc = P.lib().ckks_encrypt_cached_noalloc(ctx.handle, cache.handle, C.c_void_p(dev.data_ptr()), n, P._seed((66, n)), 3,
+                                              C.byref(b), P._stream(None))
+    assert rc == 0, P.ckks_last_error()
+    want = ctx.encrypt_cached(cache, dev, (66, n), 3)
+    torch.cuda.synchronize()
+    assert torch.equal(out.data, want.data)
+    cache.close()
+    ctx.close()
