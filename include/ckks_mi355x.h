@@ -146,13 +146,14 @@ int ckks_context_create(const ckks_params *params, int device, ckks_ctx **out);
 /* Wait for all work of the context and free it.  NULL is ignored. */
 void ckks_context_destroy(ckks_ctx *ctx);
 
-/* Tuning of the kernels on prime-field transforms (keys, ciphertext product, cache hits of
- * batches, and the encryptions and decryptions that have the lower latency through them): each
+/* Tuning of the kernels on prime-field transforms (keys, ciphertext product, batches, and the
+ * encryptions and decryptions that have the lower latency through them): each
  * thread of a workgroup holds values_per_thread ring coefficients (8, 16 or 32), so a
  * workgroup has N / values_per_thread threads (at most 1024: 8 needs N <= 8192).  Kernels on
  * complex transforms (large encryptions, decryption at N = 8192) have one shape.  The
  * setter applies to all of them (ckks_autotune chooses per kernel); the getter reports
- * the encryption kernel's.  Results are identical for every setting; only speed differs.
+ * the encryption kernel's.  Ciphertexts are identical for every setting, decoded values to a few
+ * units in the last place (their sums follow decryption's width).
  * CKKS_EINVAL for other values.  The default is 8 where allowed, else 16. */
 int ckks_context_set_ntt_width(ckks_ctx *ctx, uint32_t values_per_thread);
 int ckks_context_get_ntt_width(const ckks_ctx *ctx, uint32_t *values_per_thread);
@@ -353,7 +354,7 @@ int ckks_stream_status(ckks_ctx *ctx, void *stream);
  * subtraction, constants, rescaling, radix gather) at 0 (one workgroup per row), 2, 4,
  * 8 and 16 workgroups per compute unit, and the value-cache gather (Sec. 3.2) at 2, 4,
  * 8, 16 and 32, on trial_cts synthetic ciphertexts; keeps the fastest of each.  Reports
- * every timing.  The choices change speed only, never results.  Enqueues on the null
+ * every timing.  The choices change speed only, never ciphertexts.  Enqueues on the null
  * stream and synchronizes; allocates and frees its own scratch buffers.
  */
 typedef struct {

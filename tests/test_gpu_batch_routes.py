@@ -45,3 +45,46 @@ def test_routes_match_unbatched(log_n, width, kind, n, chunk):
     assert torch.equal(kept, decoded)
     assert torch.equal(through_ring, decoded)
     plan.close()
+
+
+@pytest.mark.parametrize("missing", [0, 1, 127, 128, 129, 900, 1700])
+@pytest.mark.parametrize("keep", [False, True])
+def test_misses_counted_on_the_device(missing, keep):
+    """At N = 8192 the device lets the misses' own launches run from half a wave of misses on (128 on
+    256 compute units), and the persistent launch take them below that."""
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2409_03568_amd as P
+
+    n, ring = 1700, 600
+    print("[gpu] counted misses %d of %d, ring %d, kept %s" % (missing, n, ring, keep), flush=True)
+    ctx = P.Context(13, 2, 50, 40)
+    ctx.keygen((44, 13))
+    px = np.full(n, 9, dtype=np.uint8)
+    px[np.random.default_rng(missing).permutation(n)[:missing]] = 200
+    dev = torch.from_numpy(px).cuda()
+    scan = torch.full((4,), 9, dtype=torch.uint8, device="cuda")
+    cache = ctx.cache_build(P.CKKS_CACHE_VALUE_TOPK, topk=1, zero_pool=4, scan_px=scan, seed=(45, 13))
+    want = ctx.encrypt_cached(cache, dev, (46, missing))
+    ctx.add_const(want, 4.0)
+    decoded = ctx.decrypt_pixels(want)
+    plan = P.BatchPlan(ctx, cache, ring, True)
+    cts = ctx.empty(n) if keep else None
+    out = torch.empty(n, dtype=torch.float64, device="cuda")
+    for rep in range(4):  # eager, then replays of the captured launches, with other work between
+        out.fill_(-1.0)
+        if keep:
+            cts.data.zero_()
+            plan.run(dev, np.array([n], dtype=np.uint64), np.array([4.0]), (46, missing), out=out, cts_out=cts)
+        else:
+            plan.run(dev, np.array([n], dtype=np.uint64), np.array([4.0]), (46, missing), out=out)
+        torch.cuda.synchronize()
+        assert torch.equal(out, decoded), rep
+        if keep:
+            assert torch.equal(cts.data, want.data), rep
+        ctx.encrypt_pixels(dev[:300].contiguous(), (47, rep))
+        torch.cuda.synchronize()
+    plan.close()
+    cache.close()
