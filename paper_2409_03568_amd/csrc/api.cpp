@@ -216,7 +216,7 @@ hipError_t encrypt_cached_ws(const ckks_ctx *ctx, const ckks_cache *cache, const
   if (cache->kind == CKKS_CACHE_VALUE_FULL)  // every value is cached: no misses
     return launch_value_gather(ctx, cache, meta, counters, hits, n, out, nullptr, st);
   const bool beside = concurrent && ctx->aux;
-  const MissRoute r = miss_route(ctx->prm.log_n, beside, n, (uint64_t)ctx->num_cus);
+  const MissRoute r = miss_route(ctx->prm.log_n, ctx->lc.L, beside, n, (uint64_t)ctx->num_cus);
   const uint64_t grid = std::min<uint64_t>(n, kListGrid);
   auto encrypt_misses = [&](hipStream_t on) {
     hipError_t f = hipSuccess;

@@ -90,14 +90,23 @@ inline bool decrypt_complex(int log_n, int prime_class, int limbs, uint64_t n, u
 //   289 pixels in tiles, N = 8192: prime-field 281, complex 302
 // After it, prime-field / complex, 1 in 6 missing: N = 4096, 1,000 pixels 181 / 214; N = 8192, 300
 // pixels 181 / 193, 1,000 pixels 282 / 292.
+// Lists of no more than a pixel per CU go by their length, but one of four primes or more at N =
+// 8192 is split over workgroups for longer than plain pixels are: workgroups without a miss leave
+// at once, so that few misses have the device, and only lists that fill its last parts lose by it.
+// Split / prime-field with 1 in 20 / 1 in 3 / all missing, after the gather, in us:
+//   3 primes, 140 pixels 109 / 128, 120 / 125, 106 / 110;  200: 126 / 134, 137 / 130, 128 / 119
+//   4 primes, 140 pixels 126 / 153, 137 / 151, 121 / 130;  234: 148 / 164, 162 / 158, 147 / 144;
+//             256: 173 / 168, 165 / 160, 148 / 147
+//   6 primes, 140 pixels 149 / 204, 167 / 201, 139 / 168;  234: 185 / 217, 207 / 209, 180 / 183
 struct MissRoute {
   uint32_t few_below, few_share;
   int few, many;      // EncKernel, -1: by n
   uint64_t few_grid;
 };
-inline MissRoute miss_route(int log_n, bool beside, uint64_t n, uint64_t cus) {
-  constexpr MissRoute by_n{0, 0, -1, -1, 0}, prime{0, 0, kEncPrime, kEncPrime, 0};
-  if (log_n == 14 || n <= (beside ? cus : cus / 2)) return by_n;
+inline MissRoute miss_route(int log_n, int primes, bool beside, uint64_t n, uint64_t cus) {
+  constexpr MissRoute by_n{0, 0, -1, -1, 0}, prime{0, 0, kEncPrime, kEncPrime, 0}, split{0, 0, kEncSplit, kEncSplit, 0};
+  if (log_n == 13 && primes > 3 && 16 * n <= 15 * cus) return split;
+  if (log_n == 14 || n <= cus) return by_n;
   if (n <= 2 * cus || (log_n < 13 && n <= 4 * cus)) return prime;
   if (beside) {
     if (log_n == 13) return n <= 4 * cus ? by_n : MissRoute{0, 2, kEncComplex, kEncComplex, cus};

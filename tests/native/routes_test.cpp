@@ -85,18 +85,27 @@ static void decryption() {
 static void cached_misses() {
   for (bool beside : {false, true})
     for (int log_n = 11; log_n <= 14; log_n++)
-      for (uint64_t n : {1ull, 128ull, 256ull, 289ull, 512ull, 1024ull, 1025ull, 4000ull, 65536ull}) {
-        const MissRoute r = miss_route(log_n, beside, n, 256);
-        const bool asked = r.few_below || r.few_share;
-        if (log_n == 14) CHECK(!asked && r.many < 0);  // kernels that are compiled
-        if (asked) CHECK(n > 512 && log_n < 14);
-        // complex encryptions of the whole device beside the gather only for many misses
-        if (asked && beside) CHECK(r.few != kEncComplex || r.few_grid == 256);
-        // after it few take the kernel of the lower latency
-        if (asked && !beside) CHECK(r.few == kEncPrime && r.many == kEncComplex);
-        if (log_n < 14 && n > 256 && n <= 512) CHECK(r.many == kEncPrime);
-        if (log_n == 11 && n > 256) CHECK(r.many == kEncPrime);
-      }
+      for (int primes = 1; primes <= 16; primes++)
+        for (uint64_t n : {1ull, 128ull, 129ull, 200ull, 240ull, 256ull, 289ull, 512ull, 1024ull, 1025ull, 4000ull, 65536ull}) {
+          const MissRoute r = miss_route(log_n, primes, beside, n, 256);
+          const bool asked = r.few_below || r.few_share;
+          if (log_n == 14) CHECK(!asked && r.many < 0);  // kernels that are compiled
+          if (asked) CHECK(n > 512 && log_n < 14);
+          // complex encryptions of the whole device beside the gather only for many misses
+          if (asked && beside) CHECK(r.few != kEncComplex || r.few_grid == 256);
+          // after it few take the kernel of the lower latency
+          if (asked && !beside) CHECK(r.few == kEncPrime && r.many == kEncComplex);
+          if (log_n < 14 && n > 256 && n <= 512) CHECK(r.many == kEncPrime);
+          if (log_n == 11 && n > 256) CHECK(r.many == kEncPrime);
+          // a short list: one launch, on either stream alike; the prime-field kernel, which takes
+          // longest for a single miss, only where it has few primes or a pixel for every CU
+          if (n > 256) continue;
+          CHECK(!asked && r.few == r.many);
+          const int kernel = r.many < 0 ? encrypt_kernel(log_n, primes, n, 256) : r.many;
+          if (log_n == 13 && primes > 2 && n <= 170) CHECK(kernel == kEncSplit);
+          if (log_n == 13 && primes > 3 && n <= 240) CHECK(kernel == kEncSplit);
+          if (log_n == 13 && primes < 3 && n > 128) CHECK(kernel == kEncPrime);
+        }
 }
 
 int main() {

@@ -75,3 +75,41 @@ def test_without_allocation(log_n, n, missing):
     assert torch.equal(out.data, want.data)
     cache.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("primes", [3, 4, 8])
+@pytest.mark.parametrize("n", [129, 171, 240, 241, 256])
+@pytest.mark.parametrize("missing", [0.0, 0.05, 1.0])
+def test_short_lists(primes, n, missing):
+    """Lists of no more than a pixel per CU, whose kernel goes by the primes too: on either stream
+    the ciphertexts of the misses are those of plain calls of at most 64 pixels."""
+    import ctypes as C
+
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2409_03568_amd as P
+
+    print("[gpu] short list %d primes, %d pixels, %.2f missing" % (primes, n, missing), flush=True)
+    ctx = P.Context(13, primes, 50, 40)
+    ctx.keygen((67, primes))
+    m = int(round(missing * n))
+    px = np.full(n, 7, dtype=np.uint8)
+    px[np.random.default_rng([primes, n, m]).permutation(n)[:m]] = 20
+    scan = torch.full((8,), 7, dtype=torch.uint8, device="cuda")
+    cache = ctx.cache_build(P.CKKS_CACHE_VALUE_TOPK, topk=1, zero_pool=4, scan_px=scan, seed=(68, primes))
+    dev, out = torch.from_numpy(px).cuda(), ctx.empty(n)
+    b = out.out_batch()
+    rc = P.lib().ckks_encrypt_cached_noalloc(ctx.handle, cache.handle, C.c_void_p(dev.data_ptr()), n, P._seed((69, n)), 3,
+                                              C.byref(b), P._stream(None))
+    assert rc == 0, P.ckks_last_error()
+    beside = ctx.encrypt_cached(cache, dev, (69, n), 3)
+    torch.cuda.synchronize()
+    assert torch.equal(out.data, beside.data)
+    for a in range(0, n, 64):
+        part = ctx.encrypt_pixels(dev[a:a + 64].contiguous(), (69, n), 3 + a).data.view(min(64, n - a), -1)
+        miss = torch.from_numpy(px[a:a + 64] != 7).cuda()
+        assert torch.equal(beside.data.view(n, -1)[a:a + 64][miss], part[miss]), a
+    cache.close()
+    ctx.close()
