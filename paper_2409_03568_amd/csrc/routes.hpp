@@ -87,9 +87,19 @@ inline bool decrypt_complex(int log_n, int prime_class, int limbs, uint64_t n, u
 //             65,536 pixels: complex, 1 per CU 7025 / 11883 / 19574, unbounded 6761 / 10037 / 14817
 //   1,024 pixels, prime-field unbounded against complex: N = 2048 109 / 112 / 123 against 144 / 142 / 148,
 //   N = 4096 134 / 137 / 169 against 148 / 163 / 191, N = 8192 217 / 270 / 357 against 206 / 224 / 310
-//   289 pixels in tiles, N = 8192: prime-field 281, complex 302
+//   N = 8192, 1 per CU / unbounded, by primes:
+//             1,200 pixels, 1 in 5 missing, 4: 210 / 214, 3 in 10: 283 / 229
+//             1,500 pixels, 1 in 5, 1: 164 / 138, 2: 205 / 171, 4: 286 / 251; 3 in 10, 4: 291 / 350, 8: 615 / 645
+//             2,000 pixels, 1 in 5, 4: 297 / 331, 3 in 10: 394 / 443;  3,000: 405 / 587, 501 / 617
+//             12,000 pixels, 1 in 5, 1: 540 / 517, 2: 782 / 901; 3 in 10, 1: 751 / 621, 2: 1055 / 965
+//             30,000 pixels, 1 in 5, 1: 1295 / 1145, 2: 1995 / 1887; 3 in 10, 1: 1802 / 1437, 4: 4976 / 4080
+//   N = 2048, 8 primes, 1 per CU / 2, 3 in 10: 1,200 pixels 187 / 161, 8,000: 603 / 548, 12,000: 867 / 812
+// Up to two pixels per CU at N = 8192, prime-field / complex by the count, 1 in 5 missing / all: beside
+// the gather, 2 primes, 400 pixels 115 / 125, 173 / 162, 4 primes 154 / 164, 249 / 219; after it, 2
+// primes 129 / 140, 170 / 168, 4 primes 181 / 194, 248 / 222, 8 primes 290 / 300, 410 / 334.
 // After it, prime-field / complex, 1 in 6 missing: N = 4096, 1,000 pixels 181 / 214; N = 8192, 300
-// pixels 181 / 193, 1,000 pixels 282 / 292.
+// pixels 181 / 193, 1,000 pixels 282 / 292.  With 8 primes, nearly all or all missing: N = 4096, 3,000
+// pixels 961 / 890, N = 2048, 12,000 pixels 1727 / 1418 (3 in 10 992 / 977).
 // Lists of no more than a pixel per CU go by their length, but one of four primes or more at N =
 // 8192 is split over workgroups for longer than plain pixels are: workgroups without a miss leave
 // at once, so that few misses have the device, and only lists that fill its last parts lose by it.
@@ -107,15 +117,22 @@ inline MissRoute miss_route(int log_n, int primes, bool beside, uint64_t n, uint
   constexpr MissRoute by_n{0, 0, -1, -1, 0}, prime{0, 0, kEncPrime, kEncPrime, 0}, split{0, 0, kEncSplit, kEncSplit, 0};
   if (log_n == 13 && primes > 3 && 16 * n <= 15 * cus) return split;
   if (log_n == 14 || n <= cus) return by_n;
+  const MissRoute counted{(uint32_t)cus + 1, 0, kEncPrime, kEncComplex, cus};  // of N = 8192
+  if (log_n == 13 && n <= 2 * cus && primes > (beside ? 1 : 2)) return counted;
   if (n <= 2 * cus || (log_n < 13 && n <= 4 * cus)) return prime;
   if (beside) {
-    if (log_n == 13) return n <= 4 * cus ? by_n : MissRoute{0, 2, kEncComplex, kEncComplex, cus};
+    if (log_n == 13 && n <= (primes < 8 ? 6 : 5) * cus) return by_n;
+    if (log_n == 13) {
+      const uint32_t share = n <= 64 * cus ? (primes < 3 ? 3 : 2) : (primes < 3 ? 5 : 3);
+      return MissRoute{0, share, kEncComplex, kEncComplex, cus};
+    }
     if (log_n == 12) return MissRoute{0, 1, kEncPrime, kEncComplex, 0};
-    return MissRoute{0, 2, kEncPrime, kEncPrime, (n < 128 * cus ? 1 : 2) * cus};
+    return MissRoute{0, 2, kEncPrime, kEncPrime, 2 * cus};
   }
-  if (log_n == 13) return MissRoute{(uint32_t)cus + 1, 0, kEncPrime, kEncComplex, cus};
-  if (log_n == 11 || n < 12 * cus) return prime;
-  return MissRoute{12 * (uint32_t)cus, 0, kEncPrime, kEncComplex, 0};
+  if (log_n == 13) return counted;
+  const uint32_t from = (log_n == 11 ? 16 : primes < 8 ? 12 : 6) * (uint32_t)cus;
+  if (n < from || (log_n == 11 && primes < 8)) return prime;
+  return MissRoute{from, 0, kEncPrime, kEncComplex, 0};
 }
 
 // How the misses of a batch (every pixel without a cache) are encrypted and decrypted: by the

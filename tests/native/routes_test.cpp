@@ -90,13 +90,19 @@ static void cached_misses() {
           const MissRoute r = miss_route(log_n, primes, beside, n, 256);
           const bool asked = r.few_below || r.few_share;
           if (log_n == 14) CHECK(!asked && r.many < 0);  // kernels that are compiled
-          if (asked) CHECK(n > 512 && log_n < 14);
+          if (asked) CHECK(n > (log_n == 13 ? 256 : 1024) && log_n < 14);
           // complex encryptions of the whole device beside the gather only for many misses
           if (asked && beside) CHECK(r.few != kEncComplex || r.few_grid == 256);
           // after it few take the kernel of the lower latency
           if (asked && !beside) CHECK(r.few == kEncPrime && r.many == kEncComplex);
-          if (log_n < 14 && n > 256 && n <= 512) CHECK(r.many == kEncPrime);
-          if (log_n == 11 && n > 256) CHECK(r.many == kEncPrime);
+          // up to two pixels per CU as many misses as there are CUs or fewer take the prime-field
+          // kernel, in one round, and more the complex one where there are primes to share
+          if (log_n < 13 && n > 256 && n <= 512) CHECK(!asked && r.many == kEncPrime);
+          if (log_n == 13 && n > 256 && n <= 512) {
+            CHECK(r.few == kEncPrime && (!asked || r.few_below == 257));
+            CHECK(r.many == (primes > (beside ? 1 : 2) ? kEncComplex : kEncPrime));
+          }
+          if (log_n == 11 && n > 256 && (beside || primes < 8)) CHECK(r.many == kEncPrime);
           // a short list: one launch, on either stream alike; the prime-field kernel, which takes
           // longest for a single miss, only where it has few primes or a pixel for every CU
           if (n > 256) continue;

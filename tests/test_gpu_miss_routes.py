@@ -78,11 +78,11 @@ def test_without_allocation(log_n, n, missing):
 
 
 @pytest.mark.parametrize("primes", [3, 4, 8])
-@pytest.mark.parametrize("n", [129, 171, 240, 241, 256])
-@pytest.mark.parametrize("missing", [0.0, 0.05, 1.0])
+@pytest.mark.parametrize("n", [129, 171, 240, 241, 256, 257, 512, 513, 1537])
+@pytest.mark.parametrize("missing", [0.0, 0.05, 0.6, 1.0])
 def test_short_lists(primes, n, missing):
-    """Lists of no more than a pixel per CU, whose kernel goes by the primes too: on either stream
-    the ciphertexts of the misses are those of plain calls of at most 64 pixels."""
+    """Lists of up to some pixels per CU, whose kernel goes by the primes too: on either stream the
+    ciphertexts of the misses are those of plain calls of at most 64 pixels."""
     import ctypes as C
 
     import torch
@@ -111,5 +111,41 @@ def test_short_lists(primes, n, missing):
         part = ctx.encrypt_pixels(dev[a:a + 64].contiguous(), (69, n), 3 + a).data.view(min(64, n - a), -1)
         miss = torch.from_numpy(px[a:a + 64] != 7).cuda()
         assert torch.equal(beside.data.view(n, -1)[a:a + 64][miss], part[miss]), a
+    cache.close()
+    ctx.close()
+
+
+@pytest.mark.parametrize("n", [1535, 1537, 4097])
+@pytest.mark.parametrize("log_n", [11, 12])
+@pytest.mark.parametrize("missing", [0.02, 1.0])
+def test_eight_primes(log_n, n, missing):
+    """Eight primes at the smaller rings, counted after the gather from a length of their own on."""
+    import ctypes as C
+
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2409_03568_amd as P
+
+    print("[gpu] misses of 8 primes N=2^%d, %d pixels, %.2f missing" % (log_n, n, missing), flush=True)
+    ctx = P.Context(log_n, 8, 36 if log_n == 12 else 30, 30 if log_n == 12 else 20)
+    ctx.keygen((70, log_n))
+    m = int(round(missing * n))
+    px = np.full(n, 7, dtype=np.uint8)
+    px[np.random.default_rng([log_n, n, m]).permutation(n)[:m]] = 20
+    scan = torch.full((8,), 7, dtype=torch.uint8, device="cuda")
+    cache = ctx.cache_build(P.CKKS_CACHE_VALUE_TOPK, topk=1, zero_pool=4, scan_px=scan, seed=(71, log_n))
+    dev, out = torch.from_numpy(px).cuda(), ctx.empty(n)
+    b = out.out_batch()
+    rc = P.lib().ckks_encrypt_cached_noalloc(ctx.handle, cache.handle, C.c_void_p(dev.data_ptr()), n, P._seed((72, n)), 3,
+                                              C.byref(b), P._stream(None))
+    assert rc == 0, P.ckks_last_error()
+    beside = ctx.encrypt_cached(cache, dev, (72, n), 3)
+    plain = ctx.encrypt_pixels(dev, (72, n), 3)
+    torch.cuda.synchronize()
+    assert torch.equal(out.data, beside.data)
+    miss = torch.from_numpy(px != 7).cuda()
+    assert torch.equal(beside.data.view(n, -1)[miss], plain.data.view(n, -1)[miss])
     cache.close()
     ctx.close()
